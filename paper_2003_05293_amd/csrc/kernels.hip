@@ -15,6 +15,7 @@
 #include "kernels.hpp"
 #include "operand_layout.hpp"
 #include "pass_tail.hpp"
+#include "pixel_pass.hpp"
 
 namespace hg {
 
@@ -28,26 +29,6 @@ __device__ __forceinline__ int32_t pixel_of(const PixelSet& ps, int32_t q) {
     return as_global(ps.perm)[k];
   }
   return q;
-}
-
-// Doubled integer offsets of pixel p from the grid centre and Q = Lx^2+Ly^2
-// (also as an integer, for the aperture test).
-struct PixCoord {
-  float Lx, Ly, Q;
-  int32_t Qi;
-};
-
-__device__ __forceinline__ PixCoord pixel_coord(int32_t p, int W, int H) {
-  const int32_t j = p / W;
-  const int32_t i = p - j * W;
-  const int32_t lx = 2 * i - (W - 1);
-  const int32_t ly = 2 * j - (H - 1);
-  PixCoord c;
-  c.Lx = (float)lx;
-  c.Ly = (float)ly;
-  c.Qi = lx * lx + ly * ly;
-  c.Q = (float)c.Qi;
-  return c;
 }
 
 // Field of eq. (1) at one pixel over spots [n0, n1): sum A_n e^{i 2 pi (t_n + th_n)}.
@@ -89,62 +70,6 @@ __device__ __forceinline__ float2 backprop_field(const SpotRec* spg, int n0, int
   return make_float2(sr, si);
 }
 
-// The same sum with the spot records in LDS (chained launches, where the
-// records change between passes of one launch): the four records of a group
-// are read together (every lane the same address: broadcast reads).
-__device__ __forceinline__ float2 backprop_field_lds(const SpotRec* recs, int n0, int n1,
-                                                     const PixCoord& c) {
-  float sr = 0.f, si = 0.f;
-  int n = n0;
-  for (; n + 3 < n1; n += 4) {
-    float4 q[4];
-    float sA[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      q[k] = *reinterpret_cast<const float4*>(&recs[n + k].cx);
-      sA[k] = recs[n + k].A;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float t = fmaf(q[k].x, c.Lx, fmaf(q[k].y, c.Ly, fmaf(q[k].z, c.Q, q[k].w)));
-      float sn, cs;
-      sincos_turns(t, sn, cs);
-      sr = fmaf(sA[k], cs, sr);
-      si = fmaf(sA[k], sn, si);
-    }
-  }
-  for (; n < n1; ++n) {
-    const float t =
-        fmaf(recs[n].cx, c.Lx, fmaf(recs[n].cy, c.Ly, fmaf(recs[n].cz, c.Q, recs[n].th)));
-    float sn, cs;
-    sincos_turns(t, sn, cs);
-    sr = fmaf(recs[n].A, cs, sr);
-    si = fmaf(recs[n].A, sn, si);
-  }
-  return make_float2(sr, si);
-}
-
-// Mixed-precision back-propagation (eq. 1): the phase of each spot in FP32
-// turns with theta folded in, t_n = phi_n(p) / 2 pi + theta_n, its cosine
-// and sine from v_sin/v_cos; the two spots of a pair have their cosines,
-// their sines and their amplitudes A_n rounded to FP16 and packed, and one
-// FP16 dot product accumulated in FP32 (v_dot2_f32_f16) adds each part of
-// the pair's terms A_n e^{i 2 pi t_n}: re += (cos_1, cos_2).(A_1, A_2),
-// im += (sin_1, sin_2).(A_1, A_2).  A spot left without a partner is paired
-// with a zero amplitude.
-__device__ __forceinline__ void mx_pair(float t1, float a1, float t2, float a2, float& sr,
-                                        float& si) {
-  float sn1, cs1, sn2, cs2;
-  sincos_turns(t1, sn1, cs1);
-  sincos_turns(t2, sn2, cs2);
-  const h2v_t a = to_h2(a1, a2);
-  sr = __builtin_amdgcn_fdot2(to_h2(cs1, cs2), a, sr, false);
-  si = __builtin_amdgcn_fdot2(to_h2(sn1, sn2), a, si, false);
-}
-__device__ __forceinline__ float turns_of(float cx, float cy, float cz, float th,
-                                          const PixCoord& c) {
-  return fmaf(cx, c.Lx, fmaf(cy, c.Ly, fmaf(cz, c.Q, th)));
-}
 // Records by scalar loads, four spots per wait.
 __device__ __forceinline__ float2 backprop_field_mx(const SpotRec* spg, int n0, int n1,
                                                     const PixCoord& c) {
@@ -169,32 +94,6 @@ __device__ __forceinline__ float2 backprop_field_mx(const SpotRec* spg, int n0, 
     mx_pair(turns_of(sp[n].cx, sp[n].cy, sp[n].cz, sp[n].th, c), sp[n].A, 0.f, 0.f, sr, si);
   return make_float2(sr, si);
 }
-// Records from LDS (a pending pass's updated state).
-__device__ __forceinline__ float2 backprop_field_mx_lds(const SpotRec* recs, int n0, int n1,
-                                                        const PixCoord& c) {
-  float sr = 0.f, si = 0.f;
-  int n = n0;
-  for (; n + 3 < n1; n += 4) {
-    float t[4], A[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float4 q = *reinterpret_cast<const float4*>(&recs[n + k].cx);
-      t[k] = turns_of(q.x, q.y, q.z, q.w, c);
-      A[k] = recs[n + k].A;
-    }
-    mx_pair(t[0], A[0], t[1], A[1], sr, si);
-    mx_pair(t[2], A[2], t[3], A[3], sr, si);
-  }
-  for (; n + 1 < n1; n += 2)
-    mx_pair(turns_of(recs[n].cx, recs[n].cy, recs[n].cz, recs[n].th, c), recs[n].A,
-            turns_of(recs[n + 1].cx, recs[n + 1].cy, recs[n + 1].cz, recs[n + 1].th, c),
-            recs[n + 1].A, sr, si);
-  if (n < n1)
-    mx_pair(turns_of(recs[n].cx, recs[n].cy, recs[n].cz, recs[n].th, c), recs[n].A, 0.f, 0.f,
-            sr, si);
-  return make_float2(sr, si);
-}
-
 // ---------------------------------------------------------------- setup ---
 
 // Row tables of the pupil for the random order (one block of kSetupThreads):
@@ -555,36 +454,6 @@ __global__ void k_gather(PixelSet ps, int32_t* __restrict__ out) {
 // addition does not depend on order, so results depend neither on
 // scheduling nor on the other jobs of the batch.
 
-__device__ __forceinline__ void forward_term(float cx, float cy, float cz, const float4& a,
-                                             float ui, float& vr, float& vi) {
-  const float t = fmaf(cx, a.x, fmaf(cy, a.y, cz * a.z));
-  float sn, cs;
-  sincos_turns(t, sn, cs);
-  // u * conj(e^{i 2 pi t})
-  vr = fmaf(a.w, cs, fmaf(ui, sn, vr));
-  vi = fmaf(ui, cs, fmaf(-a.w, sn, vi));
-}
-
-// Spot-lane layout of phase 2 for N spots.
-struct LaneMap {
-  int Lg;   // lanes per spot group (8, 16, 32 or 64)
-  int R;    // replicas per wave = 64 / Lg
-  int nch;  // spot chunks = ceil(N / Lg)
-  int S;    // pixel slices per chunk
-  int U;    // units = nch * S
-};
-
-__host__ __device__ inline LaneMap lane_map(int N) {
-  LaneMap m;
-  const int n = N < 64 ? N : 64;
-  m.Lg = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 32 : 64;
-  m.R = 64 / m.Lg;
-  m.nch = (N + m.Lg - 1) / m.Lg;
-  m.S = m.nch >= kWaves ? 1 : kWaves / m.nch;
-  m.U = m.nch * m.S;
-  return m;
-}
-
 // CHAIN: the spot records come from LDS (a.recs), the pixel index of this
 // thread in the block's first sub-tile may come prefetched (has_pre, pre_p),
 // and the block that completes the pass publishes the generation word after
@@ -675,8 +544,7 @@ __device__ void pass_block(const PassCtx& a, unsigned* grab, bool has_pre = fals
         PixCoord c{0.f, 0.f, 0.f, 0};
         if (valid) c = pixel_coord(p, a.W, a.H);
         if constexpr (MX)
-          sw[wave][lane] = PEND ? backprop_field_mx_lds(a.recs, n_lo, n_hi, c)
-                                : backprop_field_mx(sp, n_lo, n_hi, c);
+          sw[wave][lane] = backprop_field_mx(sp, n_lo, n_hi, c);
         else
           sw[wave][lane] = lds_recs ? backprop_field_lds(a.recs, n_lo, n_hi, c)
                                     : backprop_field(sp, n_lo, n_hi, c);
@@ -691,13 +559,8 @@ __device__ void pass_block(const PassCtx& a, unsigned* grab, bool has_pre = fals
               S.x += sw[w][lane].x;
               S.y += sw[w][lane].y;
             }
-            const float m2 = S.x * S.x + S.y * S.y;
-            float ur = 1.f;
-            if (m2 > 0.f) {
-              const float inv = rsqrtf(m2);
-              ur = S.x * inv;
-              ui = S.y * inv;
-            }
+            float ur;
+            unit_field(S, ur, ui);
             if (a.ap_q >= 0 || a.ill_a > 0.f) {
               const float wt = pupil_weight(c.Qi, c.Q, a.ap_q, a.ill_a);
               ur *= wt;
@@ -716,43 +579,10 @@ __device__ void pass_block(const PassCtx& a, unsigned* grab, bool has_pre = fals
       for (int k = 0; k < MAXU; ++k) {
         const int u = wave + k * kWaves;
         if (u < lm.U) {
-          const int sl = u % lm.S;
-          const int j0 = (sl * kTile) / lm.S + r, j1 = ((sl + 1) * kTile) / lm.S;
-          // one unit per wave: four pixels per step, read from LDS
-          // together, into two sums (with more units the registers go to
-          // the units' sums).  Jobs of one unit per wave always run in the
-          // MAXU = 1 launch of their round (LaunchSet), so a hologram sums
-          // in the same order alone and beside holograms of more spots.
-          float ar = vr[k], ai = vi[k], br = 0.f, bi = 0.f;
-          int j = j0;
-          if (MAXU == 1 && lm.R == 1) {
-            // one replica (r = 0): the pixel loop is uniform across the
-            // wave, so its counter and the LDS addresses stay scalar
-            int ju = __builtin_amdgcn_readfirstlane(j0);
-            const int ju1 = __builtin_amdgcn_readfirstlane(j1);
-            for (; ju + 3 < ju1; ju += 4) {
-              const float4 p0 = px[ju], p1 = px[ju + 1], p2 = px[ju + 2], p3 = px[ju + 3];
-              const float u0 = pui[ju], u1 = pui[ju + 1], u2 = pui[ju + 2], u3 = pui[ju + 3];
-              forward_term(cx[k], cy[k], cz[k], p0, u0, ar, ai);
-              forward_term(cx[k], cy[k], cz[k], p1, u1, br, bi);
-              forward_term(cx[k], cy[k], cz[k], p2, u2, ar, ai);
-              forward_term(cx[k], cy[k], cz[k], p3, u3, br, bi);
-            }
-            j = ju;
-          } else if (MAXU == 1)
-          for (; j + 3 * lm.R < j1; j += 4 * lm.R) {
-            const float4 p0 = px[j], p1 = px[j + lm.R], p2 = px[j + 2 * lm.R],
-                         p3 = px[j + 3 * lm.R];
-            const float u0 = pui[j], u1 = pui[j + lm.R], u2 = pui[j + 2 * lm.R],
-                        u3 = pui[j + 3 * lm.R];
-            forward_term(cx[k], cy[k], cz[k], p0, u0, ar, ai);
-            forward_term(cx[k], cy[k], cz[k], p1, u1, br, bi);
-            forward_term(cx[k], cy[k], cz[k], p2, u2, ar, ai);
-            forward_term(cx[k], cy[k], cz[k], p3, u3, br, bi);
-          }
-          for (; j < j1; j += lm.R) forward_term(cx[k], cy[k], cz[k], px[j], pui[j], ar, ai);
-          vr[k] = ar + br;
-          vi[k] = ai + bi;
+          // Jobs of one unit per wave always run in the MAXU = 1 launch of
+          // their round (LaunchSet), so a hologram sums in the same order
+          // alone and beside holograms of more spots.
+          forward_unit<MAXU == 1>(lm, u, r, cx[k], cy[k], cz[k], px, pui, vr[k], vi[k]);
         }
       }
       __syncthreads();
@@ -956,8 +786,6 @@ __device__ void pass_block_e(const PassCtx& a, unsigned* grab) {
   if (last) tail_final(a, &rede[0][0]);  // kWaves * MAXE >= N float2
 }
 
-static_assert(kPendMaxSpots <= kBlock, "a pending update takes one spot per thread");
-
 // Batched pass launch: blocks [descs[i].block_begin, descs[i+1].block_begin)
 // work on pass i.
 // Occupancy target (waves per SIMD): eight for the two-sincos form (all
@@ -989,9 +817,8 @@ __device__ __forceinline__ void pass_ctx(PassCtx& a, const JobDev& jb, const Pas
 // A pending pass (one unit per wave): the previous pass's update into LDS
 // (with the pixel index of this thread in the block's first sub-tile
 // requested before it, so that the two reads overlap), then the pass.
-template <bool MX>
 __device__ __forceinline__ void pending_pass(PassCtx& a, const JobDev& jb, const PassDesc& d) {
-  __shared__ SpotRec recs[kPendMaxSpots];
+  __shared__ SpotRec recs[kBlock];
   bool has_pre = false;
   int32_t pre_p = 0;
   if (!d.from_phi && a.lb < a.plan.tiles) {
@@ -999,10 +826,10 @@ __device__ __forceinline__ void pending_pass(PassCtx& a, const JobDev& jb, const
     pre_p = q < a.ps.count ? pixel_of(a.ps, q) : 0;
     has_pre = true;
   }
-  apply_pending(jb, d, a.lb == 0, recs);
+  apply_pending<kBlock>(jb, d, a.lb == 0, recs, nullptr);
   a.recs = recs;
   if (!d.defer) a.pend_row = d.prev_row;
-  pass_block<1, false, true, MX>(a, jb.grab + d.grab_slot, has_pre, pre_p);
+  pass_block<1, false, true>(a, jb.grab + d.grab_slot, has_pre, pre_p);
 }
 
 template <int MAXU, int MAXE>
@@ -1030,7 +857,7 @@ __global__ __launch_bounds__(kBlock, MAXU > 4 ? 2 : (MAXE > 16 ? 6 : 8)) void k_
   }
   if (d.pending) {
     if constexpr (MAXU == 1) {
-      pending_pass<false>(a, jb, d);
+      pending_pass(a, jb, d);
     } else {
       if (a.lb == 0 && threadIdx.x == 0) jb.status[0] = 5;  // HG_EDEVICE
     }
@@ -1039,10 +866,10 @@ __global__ __launch_bounds__(kBlock, MAXU > 4 ? 2 : (MAXE > 16 ? 6 : 8)) void k_
   pass_block<MAXU>(a, jb.grab + d.grab_slot);
 }
 
-// Compressed passes of mixed-precision jobs: the per-pixel pass with the
-// back-propagation terms as FP16 products accumulated in FP32, two spots per
-// dot product (backprop_field_mx); forward terms, sums, hand-off and update
-// as in the FP32 form.
+// Compressed passes of mixed-precision jobs of more than one spot unit per
+// wave: the per-pixel pass with the back-propagation terms as FP16 products
+// accumulated in FP32, two spots per dot product (backprop_field_mx);
+// forward terms, sums, hand-off and update as in the FP32 form.
 template <int MAXU>
 __global__ __launch_bounds__(kBlock, MAXU > 4 ? 2 : 8) void k_pass_mx(const JobDev* __restrict__ jobs,
                                                                     const PassDesc* __restrict__ descs,
@@ -1052,18 +879,6 @@ __global__ __launch_bounds__(kBlock, MAXU > 4 ? 2 : 8) void k_pass_mx(const JobD
   const JobDev& jb = jobs[d.job];
   PassCtx a;
   pass_ctx(a, jb, d);
-  if constexpr (MAXU == 1) {
-    a.tot_row = d.tot_row;
-    a.defer = d.defer;
-  }
-  if (d.pending) {
-    if constexpr (MAXU == 1) {
-      pending_pass<true>(a, jb, d);
-    } else {
-      if (a.lb == 0 && threadIdx.x == 0) jb.status[0] = 5;  // HG_EDEVICE
-    }
-    return;
-  }
   pass_block<MAXU, false, false, true>(a, jb.grab + d.grab_slot);
 }
 
@@ -1380,8 +1195,7 @@ void launch_pass_mx(const JobDev* jobs, const PassDesc* descs, int ndesc, int to
                     int max_units, hipStream_t s) {
   if (ndesc <= 0 || total_blocks <= 0) return;
   const dim3 grid(total_blocks), block(kBlock);
-  if (max_units <= 1) hipLaunchKernelGGL(k_pass_mx<1>, grid, block, 0, s, jobs, descs, ndesc);
-  else if (max_units <= 4) hipLaunchKernelGGL(k_pass_mx<4>, grid, block, 0, s, jobs, descs, ndesc);
+  if (max_units <= 4) hipLaunchKernelGGL(k_pass_mx<4>, grid, block, 0, s, jobs, descs, ndesc);
   else hipLaunchKernelGGL(k_pass_mx<16>, grid, block, 0, s, jobs, descs, ndesc);
 }
 

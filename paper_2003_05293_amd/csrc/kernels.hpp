@@ -162,6 +162,8 @@ struct JobDev {
   // core operands (see SepDesc and MxDesc); dimensions shared by both forms
   int32_t mixed;
   int32_t shared_e;    // compressed passes in the shared-exponential form
+  int32_t deferring;   // compressed passes that always take and leave deferred
+                       // updates (k_pass_defer)
   int32_t mx_steps;    // Np / 16 with Np = N rounded up to 16
   int32_t mx_cblocks;  // Wp / 16 with Wp = W rounded up to 64
   int32_t mx_rblocks;  // Hp / 16
@@ -224,7 +226,7 @@ struct PassDesc {
   SpotRec* st_out = nullptr;       // updated state, for the next pass (pending and defer)
   double2* prev_V = nullptr;       // spot fields of the previous pass (traced jobs)
 };
-constexpr int kPendMaxSpots = 256;
+constexpr int kPendMaxSpots = 512;
 
 // Final hologram of one job over a pixel set, written compactly to out[q].
 struct BackDesc {
@@ -275,9 +277,21 @@ __host__ __device__ int pass_e_width(int N);
 // max_units the largest two-phase unit count of the others.
 void launch_pass_batch(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,
                        int max_units, int e_width, hipStream_t s);
-// Compressed passes of mixed-precision jobs (the per-pixel pass with FP16
-// back-propagation products accumulated in FP32); descs and units as for
-// launch_pass_batch.
+// Compressed passes of `deferring` jobs: N <= kDeferMaxSpots (FP32) or
+// kBlock (mixed: FP16 back-propagation products accumulated in FP32).  With
+// one descriptor, `head` holds what the start of its pass reads.
+constexpr int kDeferMaxSpots = 512;
+struct PassHead {
+  const SpotRec* st = nullptr;              // state before the previous pass's update
+  const unsigned long long* tot = nullptr;  // the previous pass's total set (null: no update)
+  const int32_t* perm = nullptr;
+  int32_t start = 0, P = 0, count = 0, N = 0, W = 0, H = 0;
+  int32_t job = 0;                          // index of the job in the launch's table
+};
+void launch_pass_defer(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,
+                       int max_spots, bool mixed, const PassHead& head, hipStream_t s);
+// Compressed passes of the other mixed-precision jobs (more than one spot
+// unit per wave); descs and units as for launch_pass_batch.
 void launch_pass_mx(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,
                     int max_units, hipStream_t s);
 void launch_backprop_batch(const JobDev* jobs, const BackDesc* descs, int ndesc,

@@ -1,0 +1,230 @@
+// Compressed passes that take and leave deferred weight updates (paper
+// section 2: eq. (1) back-propagation and eq. (3) forward projection over one
+// window of the random pixel order, eqs. (4)-(6) of the previous pass at the
+// start): every compressed pass of an FP32 job with separable full-grid
+// passes (N <= kDeferMaxSpots) or of a mixed job of one spot unit per wave.
+//
+// The arithmetic and the order of every sum are those of the per-pixel pass
+// (k_pass_batch, k_pass_mx), so the results are its results bit for bit.
+//
+// Bound.  One hologram at 1152^2, N = 100, c = 1/16 (1296 tiles, five per
+// compute unit): a chain of about 4 us (launch, the reads of state and totals,
+// the update) in front of about 5 us of vector issue (38 cycles per 64 pairs
+// back, 44 forward), and the additions at the end.  What this form takes off
+// the per-pixel pass with deferred updates: the descriptor and job reads in
+// front of everything else (arguments in registers), the totals' trips to
+// memory (plain loads, shared in the L2), one of the tile's barriers with the
+// normalisation of all four waves' pixels by one wave, half of the addition
+// phase (one component per thread instead of two), the serial update on the
+// same SIMD for all blocks of a compute unit, and 16 VGPRs (60 instead of 76:
+// eight waves per SIMD instead of six).  Hologram time, before and after:
+// 1152^2, N = 100: 481 to 413 us (pass 14.2 to 12 us); 1920 x 1152 under the
+// pupil, N = 52, c = 1/8: 442 to 302 us; N = 300, c = 1/16: 1250 to 1051 us
+// (no hand-off, no update in the tail); mixed, N = 100: 502 to 405 us; 32
+// holograms of 1152^2 per batch: 8.54 to 7.32 ms.
+#include <math.h>
+
+#include "device_common.hpp"
+#include "device_math.hpp"
+#include "kernels.hpp"
+#include "pass_tail.hpp"
+#include "pixel_pass.hpp"
+
+namespace hg {
+
+namespace {
+
+// What the start of a pass reads, uniform across the block.
+struct PassStart {
+  const SpotRec* st;               // spot state before the previous pass's update
+  const unsigned long long* tot;   // the previous pass's total set (null: no update)
+  const int32_t* perm;
+  int start, P, count, N, W, H;
+};
+
+__device__ __forceinline__ int32_t window_pixel(const PassStart& h, int q) {
+  int64_t k = (int64_t)h.start + q;
+  if (k >= h.P) k -= h.P;
+  return as_global(h.perm)[k];
+}
+
+// One pass of one job.  MAXU: spot units per wave (1: N <= 256, 2: N <= 512).
+//
+// A block takes its tiles of 64 pixels in turn.  Per 64 pixels:
+//  phase 1  lane = pixel, wave w adds the spots [w N/4, (w+1) N/4); the four
+//           shares meet in LDS (the one barrier of the tile's arithmetic);
+//  u        every wave adds the shares of all 64 pixels in wave order,
+//           normalises, and keeps u in its own LDS rows: no wave waits for
+//           another's normalisation, which runs at the same time on the four
+//           SIMDs;
+//  phase 2  lanes = spots over the wave's pixels, as in the per-pixel pass.
+// Then each component of the tile's sums is formed by one thread and added to
+// the pass's total set, re and im in neighbouring lanes.
+template <int MAXU, bool MX>
+__device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& plan, int lb,
+                                            int tot_row, unsigned long long* acc, float ill_a,
+                                            const SpotRec* recs, PixCoord c) {
+  __shared__ float2 sw[2][kWaves][kTile];
+  __shared__ float4 px[kWaves][kTile];
+  __shared__ float pui[kWaves][kTile];
+  __shared__ float2 red[kWaves * MAXU][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int N = h.N;
+  const LaneMap lm = lane_map(N);
+  const int g = lane % lm.Lg, r = lane / lm.Lg;
+  float cx[MAXU], cy[MAXU], cz[MAXU];
+#pragma unroll
+  for (int k = 0; k < MAXU; ++k) {
+    const int u = wave + k * kWaves;
+    const int n = (u / lm.S) * lm.Lg + g;
+    cx[k] = cy[k] = cz[k] = 0.f;
+    if (u < lm.U && n < N) {
+      cx[k] = recs[n].cx;
+      cy[k] = recs[n].cy;
+      cz[k] = recs[n].cz;
+    }
+  }
+  const int n_lo = (wave * N) / kWaves, n_hi = ((wave + 1) * N) / kWaves;
+  const double scale = ldexp(1.0, plan.shift);
+  bool first = true;
+  int buf = 0;
+  for (int tile = lb; tile < plan.tiles; tile += plan.blocks) {
+    float vr[MAXU], vi[MAXU];
+#pragma unroll
+    for (int k = 0; k < MAXU; ++k) vr[k] = vi[k] = 0.f;
+    for (int st = 0; st < plan.sub; ++st) {
+      const int32_t q = (tile * plan.sub + st) * kTile + lane;
+      const bool valid = q < h.count;
+      if (!first) c = pixel_coord(valid ? window_pixel(h, q) : 0, h.W, h.H);
+      first = false;
+      if (!valid) c = PixCoord{0.f, 0.f, 0.f, 0};
+      sw[buf][wave][lane] =
+          MX ? backprop_field_mx_lds(recs, n_lo, n_hi, c) : backprop_field_lds(recs, n_lo, n_hi, c);
+      __syncthreads();
+      {
+        float4 rec = make_float4(0.f, 0.f, 0.f, 0.f);
+        float ui = 0.f;
+        if (valid) {
+          float2 S = sw[buf][0][lane];
+#pragma unroll
+          for (int w = 1; w < kWaves; ++w) {
+            S.x += sw[buf][w][lane].x;
+            S.y += sw[buf][w][lane].y;
+          }
+          float ur;
+          unit_field(S, ur, ui);
+          if (ill_a > 0.f) {
+            const float wt = pupil_weight(c.Qi, c.Q, -1, ill_a);
+            ur *= wt;
+            ui *= wt;
+          }
+          rec = make_float4(c.Lx, c.Ly, c.Q, ur);
+        }
+        px[wave][lane] = rec;
+        pui[wave][lane] = ui;
+      }
+      // (the wave's own rows: its LDS accesses complete in order)
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int k = 0; k < MAXU; ++k) {
+        const int u = wave + k * kWaves;
+        if (u >= lm.U) continue;
+        // (the order of the sums goes by the job's own unit count, also where
+        // it shares the launch with jobs of more spots)
+        if (MAXU == 1 || lm.U <= kWaves)
+          forward_unit<true>(lm, u, r, cx[k], cy[k], cz[k], px[wave], pui[wave], vr[k], vi[k]);
+        else
+          forward_unit<false>(lm, u, r, cx[k], cy[k], cz[k], px[wave], pui[wave], vr[k], vi[k]);
+      }
+      buf ^= 1;  // the next shares go to the other rows: one barrier is enough
+    }
+#pragma unroll
+    for (int k = 0; k < MAXU; ++k) {
+      const int u = wave + k * kWaves;
+      if (u < lm.U) red[u][lane] = make_float2(vr[k], vi[k]);
+    }
+    __syncthreads();
+    unsigned long long* out =
+        acc + (int64_t)(tot_row * kAccReplicas + tile % kAccReplicas) * N * kAccSpotWords;
+    for (int x = threadIdx.x; x < 2 * N; x += kBlock) {
+      const int n = x >> 1, part = x & 1;
+      const int ch = n / lm.Lg, gg = n % lm.Lg;
+      float s = 0.f;
+      for (int sl = 0; sl < lm.S; ++sl)
+        for (int rr = 0; rr < lm.R; ++rr)
+          s += reinterpret_cast<const float*>(&red[ch * lm.S + sl][rr * lm.Lg + gg])[part];
+      atomicAdd(out + x, (unsigned long long)llrint((double)s * scale));
+    }
+    if (tile + plan.blocks < plan.tiles) __syncthreads();  // red is rewritten
+  }
+}
+
+// One round of deferring passes.  With one pass in the launch (ndesc == 1)
+// its start comes as kernel arguments, the first sixteen dwords of which are
+// in registers when the wave begins: the reads of the state, the totals and
+// the pixel order then start without waiting for the descriptor and, after
+// it, the job record (two memory round trips), and `jobs` is that job.
+template <int MAXU, bool MX>
+__global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
+    const SpotRec* st, const unsigned long long* tot, const int32_t* perm, int32_t start, int32_t P,
+    int32_t count, int32_t N, uint32_t WH, int32_t ndesc, const PassDesc* __restrict__ descs,
+    const JobDev* __restrict__ jobs) {
+  constexpr int kMaxN = MAXU > 1 ? kDeferMaxSpots : kBlock;
+  __shared__ SpotRec recs[kMaxN];
+  PassStart h{st, tot, perm, start, P, count, N, (int)(WH & 0xffffu), (int)(WH >> 16)};
+  const PassDesc* dp = descs;
+  const JobDev* jp = jobs;
+  int lb = blockIdx.x;
+  if (ndesc > 1) {
+    dp += find_desc(descs, ndesc, blockIdx.x);
+    jp += dp->job;
+    lb -= dp->block_begin;
+    h = PassStart{dp->pending ? dp->st_in : jp->sp,
+                  dp->pending ? jp->acc + (int64_t)dp->prev_row * kAccReplicas * jp->N * kAccSpotWords
+                              : nullptr,
+                  dp->ps.perm, (int)dp->ps.start, dp->ps.M, dp->ps.count, jp->N, jp->W, jp->H};
+  }
+  const PassDesc& d = *dp;
+  const JobDev& jb = *jp;
+  // the pixel of this lane in the block's first 64, requested with the state
+  const int q0 = lb * d.plan.sub * kTile + (int)(threadIdx.x & 63);
+  const int32_t p0 = q0 < h.count ? window_pixel(h, q0) : 0;
+  // the updating waves: another pair of the four SIMDs for each of the blocks
+  // that share a compute unit (blocks 256 apart)
+  const int vt = (int)((threadIdx.x + 64u * (unsigned)((lb >> 8) & 3)) & (unsigned)(kBlock - 1));
+  PixCoord c;
+  if (h.tot) {
+    PendingState<kMaxN> ps;
+    ps.load(h.st, h.tot, h.N, vt);
+    c = pixel_coord(p0, h.W, h.H);
+    ps.apply(jb, d, h.N, lb == 0, vt, recs, nullptr);
+  } else {
+    c = pixel_coord(p0, h.W, h.H);
+    const HG_GLOBAL float* src = as_global(reinterpret_cast<const float*>(h.st));
+    float* dst = reinterpret_cast<float*>(recs);
+    for (int k = threadIdx.x; k < (int)(sizeof(SpotRec) / sizeof(float)) * h.N; k += kBlock)
+      dst[k] = src[k];
+    __syncthreads();
+  }
+  defer_tiles<MAXU, MX>(h, d.plan, lb, d.tot_row, jb.acc, jb.ill_a, recs, c);
+}
+
+}  // namespace
+
+void launch_pass_defer(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,
+                       int max_spots, bool mixed, const PassHead& head, hipStream_t s) {
+  if (ndesc <= 0 || total_blocks <= 0) return;
+  const dim3 grid(total_blocks), block(kBlock);
+  const JobDev* j = ndesc == 1 ? jobs + head.job : jobs;
+  const uint32_t WH = (uint32_t)head.W | ((uint32_t)head.H << 16);
+#define HG_LAUNCH(U, M)                                                                          \
+  hipLaunchKernelGGL((k_pass_defer<U, M>), grid, block, 0, s, head.st, head.tot, head.perm,      \
+                     head.start, head.P, head.count, head.N, WH, ndesc, descs, j)
+  if (mixed) HG_LAUNCH(1, true);
+  else if (max_spots <= kBlock) HG_LAUNCH(1, false);
+  else HG_LAUNCH(2, false);
+#undef HG_LAUNCH
+}
+
+}  // namespace hg

@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kBlock, 3) void k_mx_pass(const JobDev* __restrict_
                                                     const MxDesc* __restrict__ descs, int ndesc) {
   extern __shared__ float2 cs[];                     // [Np] C_n = A_n e^{i theta_n}
   __shared__ uint32_t us[kWaves][16][kMxTileW + 4];  // u of each wave's rows (half pairs)
-  __shared__ SpotRec recs[kPendMaxSpots];            // pending: the updated records
+  __shared__ SpotRec recs[kBlock];            // pending: the updated records
   __shared__ float2 red[kWaves][64];
   const int di = find_desc(descs, ndesc, blockIdx.x);
   const MxDesc& d = descs[di];
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kBlock, 3) void k_mx_pass(const JobDev* __restrict_
   if (MODE != kMxFromPhi) {
     if (d.pending) {
       // the previous pass's deferred update, C_n formed as its tail would
-      apply_pending(jb, d, lb == 0, recs, cs);
+      apply_pending<kBlock>(jb, d, lb == 0, recs, cs);
       for (int n = N + threadIdx.x; n < 16 * S16; n += kBlock) cs[n] = make_float2(0.f, 0.f);
     } else {
       for (int n = threadIdx.x; n < 16 * S16; n += kBlock) {

@@ -103,19 +103,51 @@ __device__ bool tail_group(const PassCtx& a, int g, int* flag) {
 // A spot field enters as the FP64 mean of the exact sums rounded to FP32.
 __device__ __forceinline__ float2 field32(double2 t) { return make_float2((float)t.x, (float)t.y); }
 __device__ __forceinline__ float mag32(float2 v) { return sqrtf(fmaf(v.x, v.x, v.y * v.y)); }
+// Sum over a wave, valid in lane 0, as the tree over lanes 32, 16, 8, 4, 2
+// and 1 apart.  Halves and rows are exchanged by lane swaps, the lanes of a
+// row by rotations: in every step the lane that is read holds the same bits
+// as the one that many lanes above (the sums are symmetric), and no step
+// goes through LDS.
+__device__ __forceinline__ float swap_add(float x, bool rows) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = rows ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
+                      : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+template <int N>
+__device__ __forceinline__ float ror_add(float x) {
+  return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                           0, __builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_tree_sum(float x) {
+  x = swap_add(x, false);
+  x = swap_add(x, true);
+  x = ror_add<8>(x);
+  x = ror_add<4>(x);
+  x = ror_add<2>(x);
+  return ror_add<1>(x);
+}
 // mean_n |V_n| (eq. 4), the same in every thread of the block: thread t
 // adds |V_n| for n = t, t + kBlock, ... in that order, starting from 0 (s
 // is that thread sum); the thread sums are added in a fixed tree within
 // each wave, then the wave sums in wave order.  Every thread must call it
-// (it holds a block barrier).
-__device__ __forceinline__ float block_mean_of(float s, int N) {
+// (it holds a block barrier); t is the thread's index, or that of a
+// whole-wave rotation of the block.
+__device__ __forceinline__ float block_mean_of(float s, int N, int t) {
   __shared__ float wsum[kWaves];
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off);
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = s;
+  s = wave_tree_sum(s);
+  if ((t & 63) == 0) wsum[t >> 6] = s;
   __syncthreads();
   float total = wsum[0];
   for (int w = 1; w < kWaves; ++w) total += wsum[w];
   return total / (float)N;
+}
+// The angle of v in turns.  A function of its own, never inlined: the
+// library's atan2f carries a division of relaxed accuracy whose form depends
+// on what the compiler merges it with, and the immediate and the deferred
+// update, in whichever kernel, have to give the same bits.
+__device__ __attribute__((noinline)) float arg_turns(float2 v) {
+  return atan2f(v.y, v.x) * 0.15915494309189535f;
 }
 // false (record unchanged) where the weight would come out zero or not finite
 __device__ __forceinline__ bool update_rec(SpotRec& r, float2 v, float mag, float mean) {
@@ -123,7 +155,7 @@ __device__ __forceinline__ bool update_rec(SpotRec& r, float2 v, float mag, floa
   if (!(mag > 0.f) || !isfinite(w)) return false;
   r.w = w;
   r.A = w * r.a0;
-  r.th = atan2f(v.y, v.x) * 0.15915494309189535f;
+  r.th = arg_turns(v);
   return true;
 }
 
@@ -170,7 +202,7 @@ __device__ void tail_final(const PassCtx& a, float2* vs) {
       a.counters[k * kCounterStride] = 0u;
   }
   if (!a.update) return;
-  const float mean = block_mean_of(msum, N);
+  const float mean = block_mean_of(msum, N, threadIdx.x);
   for (int n = threadIdx.x; n < N; n += kBlock) {
     const float2 v = vs[n];
     const float mag = mag32(v);
@@ -191,84 +223,126 @@ __device__ void tail_final(const PassCtx& a, float2* vs) {
 
 // Pending pass: every block adds the rows of the previous pass's total set
 // (integer sums: the total that a hand-off would have formed), applies that
-// pass's update to the state before it (d.st_in) and keeps the result in
-// recs (LDS), with the arithmetic and the mean of tail_final (one spot per
-// thread); with cl, also C_n = A_n e^{i theta_n} in FP32 (LDS), formed as
-// tail_final forms it.  Block 0 (lead) also clears
-// the total set two passes back, stores the state for the next pass when
-// this pass defers in turn (the final state, in the final hologram), the
-// previous V when traced, and the status.  N <= kPendMaxSpots <= kBlock.
-// D: PassDesc or SepDesc.
-template <typename D>
-__device__ void apply_pending(const JobDev& jb, const D& d, bool lead, SpotRec* recs,
-                              float2* cl = nullptr) {
-  const int N = jb.N;
-  const int n = threadIdx.x;
-  if (lead && d.clear_row >= 0) {
-    HG_GLOBAL unsigned long long* q =
-        as_global_mut(jb.acc + (int64_t)d.clear_row * kAccReplicas * N * kAccSpotWords);
-    for (int k = threadIdx.x; k < kAccReplicas * N * kAccSpotWords; k += kBlock)
-      __hip_atomic_store(q + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  double2 t = make_double2(0.0, 0.0);
-  // the record as eight words (a struct copy through a generic pointer
-  // would go through the stack)
-  constexpr int kWords = (int)(sizeof(SpotRec) / sizeof(float));
-  float f[kWords];
+// pass's update to the state before it and keeps the result in recs (LDS),
+// with the arithmetic and the mean of tail_final; with cl, also
+// C_n = A_n e^{i theta_n} in FP32 (LDS), formed as tail_final forms it.
+// Block 0 (lead) also clears the total set two passes back, stores the state
+// for the next pass when this pass defers in turn (the final state, in the
+// final hologram), the previous V when traced, and the status.  Threads of
+// index vt < kBlock take the spots vt, vt + kBlock, ... < N <= MAXN; vt is
+// the thread's index, or that of a whole-wave rotation of the block (the
+// waves of the blocks that share a compute unit then do this serial part on
+// different SIMDs).
+//
+// load() only requests the values, so that what the caller does before
+// apply() overlaps their way.  The totals were completed by the launch before
+// this one: ordinary 16-byte loads read them, which the blocks of an XCD
+// share in its L2 (device-scope loads of 8 bytes, each a trip to memory,
+// took 0.65 us more per compressed pass of 1296 blocks at N = 100).
+typedef unsigned long long ull2_t __attribute__((ext_vector_type(2)));
+typedef float flt4_t __attribute__((ext_vector_type(4)));
+template <int MAXN>
+struct PendingState {
+  static constexpr int kPer = (MAXN + kBlock - 1) / kBlock;
+  static_assert(sizeof(SpotRec) == 2 * sizeof(flt4_t), "a record is two 16-byte words");
+  ull2_t sum[kPer];  // modulo 2^64: the exact total fits
+  flt4_t lo[kPer], hi[kPer];
+
+  // st: the state before the update; tot: the total set's first row.
+  __device__ __forceinline__ void load(const SpotRec* st, const unsigned long long* tot, int N,
+                                       int vt) {
 #pragma unroll
-  for (int k = 0; k < kWords; ++k) f[k] = 0.f;
-  if (n < N) {
-    const HG_GLOBAL unsigned long long* tot =
-        as_global(jb.acc + ((int64_t)d.prev_row * kAccReplicas * N + n) * kAccSpotWords);
-    unsigned long long sre = 0ull, sim = 0ull;  // modulo 2^64: the exact total fits
+    for (int i = 0; i < kPer; ++i) {
+      const int n = vt + i * kBlock;
+      sum[i] = ull2_t{0ull, 0ull};
+      lo[i] = hi[i] = flt4_t{0.f, 0.f, 0.f, 0.f};
+      if (n < N) {
+        const HG_GLOBAL ull2_t* q = as_global(reinterpret_cast<const ull2_t*>(tot)) + n;
+        ull2_t v[kAccReplicas];
 #pragma unroll
-    for (int r = 0; r < kAccReplicas; ++r) {
-      const HG_GLOBAL unsigned long long* t = tot + (int64_t)r * N * kAccSpotWords;
-      sre += __hip_atomic_load(t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      sim += __hip_atomic_load(t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    const long long re = (long long)sre, im = (long long)sim;
-    t = make_double2((double)re * d.prev_inv, (double)im * d.prev_inv);
-    const HG_GLOBAL float* src = as_global(reinterpret_cast<const float*>(d.st_in + n));
+        for (int r = 0; r < kAccReplicas; ++r) v[r] = q[(int64_t)r * N];
+        const HG_GLOBAL flt4_t* s = as_global(reinterpret_cast<const flt4_t*>(st + n));
+        lo[i] = s[0];
+        hi[i] = s[1];
 #pragma unroll
-    for (int k = 0; k < kWords; ++k) f[k] = src[k];
-  }
-  const float mean = block_mean_of(n < N ? mag32(field32(t)) : 0.f, N);
-  if (n < N) {
-    if (lead && d.prev_V) {
-      HG_GLOBAL double* v = as_global_mut(reinterpret_cast<double*>(d.prev_V + n));
-      v[0] = t.x;
-      v[1] = t.y;
-    }
-    SpotRec r;
-    __builtin_memcpy(&r, f, sizeof(r));
-    const float2 v = field32(t);
-    const float mag = mag32(v);
-    const bool ok = update_rec(r, v, mag, mean);
-    if (!ok && lead) jb.status[0] = 4;  // HG_ENUMERIC
-    if (cl) {  // C_n = A_n e^{i theta_n}
-      float2 C;
-      if (ok) {
-        const float Am = r.A / mag;  // as tail_final forms it
-        C = make_float2(Am * v.x, Am * v.y);
-      } else {
-        float sn, cs;
-        sincos_turns(r.th, sn, cs);
-        C = make_float2(r.A * cs, r.A * sn);
+        for (int r = 0; r < kAccReplicas; ++r) sum[i] += v[r];
       }
-      cl[n] = C;
-    }
-    __builtin_memcpy(f, &r, sizeof(r));
-    float* dst = reinterpret_cast<float*>(recs + n);
-#pragma unroll
-    for (int k = 0; k < kWords; ++k) dst[k] = f[k];
-    if (lead && d.st_out) {
-      HG_GLOBAL float* out = as_global_mut(reinterpret_cast<float*>(d.st_out + n));
-#pragma unroll
-      for (int k = 0; k < kWords; ++k) out[k] = f[k];
     }
   }
-  __syncthreads();
+
+  // D: PassDesc, SepDesc or MxDesc.  Every thread calls it (block barriers).
+  template <typename D>
+  __device__ __forceinline__ void apply(const JobDev& jb, const D& d, int N, bool lead, int vt,
+                                        SpotRec* recs, float2* cl) const {
+    double2 t[kPer];
+    float msum = 0.f;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      t[i] = make_double2((double)(long long)sum[i][0] * d.prev_inv,
+                          (double)(long long)sum[i][1] * d.prev_inv);
+      if (vt + i * kBlock < N) msum += mag32(field32(t[i]));
+    }
+    const float mean = block_mean_of(msum, N, vt);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int n = vt + i * kBlock;
+      if (n >= N) continue;
+      SpotRec r;
+      r.cx = lo[i][0];
+      r.cy = lo[i][1];
+      r.cz = lo[i][2];
+      r.th = lo[i][3];
+      r.A = hi[i][0];
+      r.a0 = hi[i][1];
+      r.w = hi[i][2];
+      r.pad = hi[i][3];
+      const float2 v = field32(t[i]);
+      const float mag = mag32(v);
+      const bool ok = update_rec(r, v, mag, mean);
+      if (!ok && lead) jb.status[0] = 4;  // HG_ENUMERIC
+      if (cl) {  // C_n = A_n e^{i theta_n}
+        float2 C;
+        if (ok) {
+          const float Am = r.A / mag;  // as tail_final forms it
+          C = make_float2(Am * v.x, Am * v.y);
+        } else {
+          float sn, cs;
+          sincos_turns(r.th, sn, cs);
+          C = make_float2(r.A * cs, r.A * sn);
+        }
+        cl[n] = C;
+      }
+      const flt4_t a = {r.cx, r.cy, r.cz, r.th}, b = {r.A, r.a0, r.w, r.pad};
+      flt4_t* dst = reinterpret_cast<flt4_t*>(recs + n);
+      dst[0] = a;
+      dst[1] = b;
+      if (lead && d.st_out) {
+        HG_GLOBAL flt4_t* out = as_global_mut(reinterpret_cast<flt4_t*>(d.st_out + n));
+        out[0] = a;
+        out[1] = b;
+      }
+      if (lead && d.prev_V) {
+        HG_GLOBAL double* q = as_global_mut(reinterpret_cast<double*>(d.prev_V + n));
+        q[0] = t[i].x;
+        q[1] = t[i].y;
+      }
+    }
+    __syncthreads();
+    if (lead && d.clear_row >= 0) {
+      HG_GLOBAL unsigned long long* q =
+          as_global_mut(jb.acc + (int64_t)d.clear_row * kAccReplicas * N * kAccSpotWords);
+      for (int k = threadIdx.x; k < kAccReplicas * N * kAccSpotWords; k += kBlock)
+        __hip_atomic_store(q + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+};
+template <int MAXN, typename D>
+__device__ __forceinline__ void apply_pending(const JobDev& jb, const D& d, bool lead,
+                                              SpotRec* recs, float2* cl) {
+  PendingState<MAXN> ps;
+  ps.load(d.st_in, jb.acc + (int64_t)d.prev_row * kAccReplicas * jb.N * kAccSpotWords, jb.N,
+          threadIdx.x);
+  ps.apply(jb, d, jb.N, lead, threadIdx.x, recs, cl);
 }
 
 // Chained launch: the update of this pass is complete (this block's state

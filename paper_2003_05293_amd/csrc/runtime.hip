@@ -449,6 +449,13 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
   j.mixed = s.precision == HG_PREC_MIXED ? 1 : 0;
   j.shared_e = (!j.mixed && tp.pass_form == 1 && pass_e_width(s.N) > 0) ? 1 : 0;
   L.separable = !j.mixed && tp.separable_full && !s.full_direct;
+  // compressed passes without an update of their own, where every pass up to
+  // the final hologram takes deferred updates (a chained launch hands its
+  // updates over inside the launch instead)
+  j.deferring = (j.compressed && s.phi && !tp.chain_passes && !j.shared_e &&
+                 (j.mixed ? pass_units_per_wave(s.N) == 1 : L.separable && s.N <= kDeferMaxSpots))
+                    ? 1
+                    : 0;
   L.plan_all = plan_pass(j.M, tp.full_block_cap);
   L.plan_sub = j.compressed ? plan_pass(j.m, tp.subset_block_cap) : L.plan_all;
   L.plan_sep = plan_sep(j.W, j.H);
@@ -584,13 +591,13 @@ JobDev bind_job(const JobLayout& L, const JobSpec& s, char* base, const double* 
 namespace {
 // Deferred updates.  Pass it of job j (1..I; I + 1 is the final hologram)
 // can apply the previous pass's update at its start, and so let that pass
-// stop after its sums: the per-pixel compressed passes of one spot unit per
-// wave (FP32 or mixed), the FP32 separable full-grid passes and final
-// hologram, and the mixed full-grid pass and final hologram of a CS-WGS
-// job, for N <= kPendMaxSpots.
+// stop after its sums: the compressed passes of deferring jobs and the
+// per-pixel ones of one spot unit per wave, the FP32 separable full-grid
+// passes and final hologram, and the mixed full-grid pass and final hologram
+// of a CS-WGS job, for N <= kPendMaxSpots (mixed: kBlock).
 bool pend_capable(const JobDev& j, const JobLayout& L, int it) {
-  if (j.N > kPendMaxSpots || !j.sp_alt) return false;
-  if (j.compressed && it < j.iterations) return j.defer_ok && !j.shared_e;
+  if (j.N > (j.mixed ? kBlock : kPendMaxSpots) || !j.sp_alt) return false;
+  if (j.compressed && it < j.iterations) return j.deferring || (j.defer_ok && !j.shared_e);
   // mixed CS-WGS: the full-grid pass and the final hologram (the exact sums
   // of a mixed job are kept only with compressed passes)
   if (j.mixed) return j.compressed && (it == j.iterations || (it > j.iterations && j.phi));
@@ -707,19 +714,39 @@ void LaunchSet::add_forward_mx(const JobDev& j, const JobLayout& L, int index) {
   mx_mode = kMxFromPhi;
 }
 
+namespace {
+PassHead pass_head(const JobDev& j, const PassDesc& d) {
+  PassHead h;
+  h.st = d.pending ? d.st_in : j.sp;
+  h.tot = d.pending ? j.acc + (int64_t)d.prev_row * kAccReplicas * j.N * kAccSpotWords : nullptr;
+  h.perm = d.ps.perm;
+  h.start = (int32_t)d.ps.start;
+  h.P = d.ps.M;
+  h.count = d.ps.count;
+  h.N = j.N;
+  h.W = j.W;
+  h.H = j.H;
+  h.job = d.job;
+  return h;
+}
+}  // namespace
+
 void LaunchSet::add_iteration(const JobDev& j, const JobLayout& L, int it, int index) {
   const bool sub = j.compressed && it < j.iterations;
+  if (sub && j.deferring) {
+    const PassDesc d = iteration_desc(j, L, it, index, j.mixed ? mxp_blocks : dfr_blocks);
+    std::vector<PassDesc>& list = j.mixed ? mxp : dfr;
+    if (list.empty()) (j.mixed ? mxp_head : dfr_head) = pass_head(j, d);
+    list.push_back(d);
+    (j.mixed ? mxp_blocks : dfr_blocks) += d.plan.blocks;
+    if (!j.mixed) dfr_spots = std::max(dfr_spots, j.N);
+    return;
+  }
   if (j.mixed && sub) {  // per-pixel compressed pass, FP16 back-propagation
-    const int u = pass_units_per_wave(j.N);
-    const PassDesc d = iteration_desc(j, L, it, index, u > 1 ? mxw_blocks : mxp_blocks);
-    if (u > 1) {
-      mxw.push_back(d);
-      mxw_blocks += d.plan.blocks;
-      mxw_units = std::max(mxw_units, u);
-    } else {
-      mxp.push_back(d);
-      mxp_blocks += d.plan.blocks;
-    }
+    const PassDesc d = iteration_desc(j, L, it, index, mxw_blocks);
+    mxw.push_back(d);
+    mxw_blocks += d.plan.blocks;
+    mxw_units = std::max(mxw_units, pass_units_per_wave(j.N));
     return;
   }
   if (j.mixed) {
@@ -788,7 +815,8 @@ void LaunchSet::add_final(const JobDev& j, const JobLayout& L, int index) {
 }
 
 size_t LaunchSet::bytes() const {
-  return align_up(sizeof(PassDesc) * pass.size(), 256) + align_up(sizeof(PassDesc) * wide.size(), 256) +
+  return align_up(sizeof(PassDesc) * dfr.size(), 256) +
+         align_up(sizeof(PassDesc) * pass.size(), 256) + align_up(sizeof(PassDesc) * wide.size(), 256) +
          align_up(sizeof(SepDesc) * sep.size(), 256) +
          align_up(sizeof(BackDesc) * back.size(), 256) + align_up(sizeof(MxDesc) * mx.size(), 256) +
          align_up(sizeof(PassDesc) * mxp.size(), 256) + align_up(sizeof(PassDesc) * mxw.size(), 256);
@@ -802,6 +830,7 @@ size_t LaunchSet::stage(char* host, char* dev) {
     o = align_up(o + n, 256);
     return dev + at;
   };
+  d_dfr = reinterpret_cast<const PassDesc*>(put(dfr.data(), sizeof(PassDesc) * dfr.size()));
   d_pass = reinterpret_cast<const PassDesc*>(put(pass.data(), sizeof(PassDesc) * pass.size()));
   d_wide = reinterpret_cast<const PassDesc*>(put(wide.data(), sizeof(PassDesc) * wide.size()));
   d_sep = reinterpret_cast<const SepDesc*>(put(sep.data(), sizeof(SepDesc) * sep.size()));
@@ -823,8 +852,10 @@ const char* pass_name(const std::vector<PassDesc>& a, const std::vector<PassDesc
 
 const char* LaunchSet::pass_only_name() const {
   const bool fp32 = !pass.empty() || !wide.empty(), mixed = !mxp.empty() || !mxw.empty();
-  if (fp32 == mixed || !sep.empty() || !back.empty() || !mx.empty()) return nullptr;
-  return fp32 ? pass_name(pass, wide) : "k_mxp_subset";
+  if ((int)!dfr.empty() + (int)fp32 + (int)mixed != 1 || !sep.empty() || !back.empty() ||
+      !mx.empty())
+    return nullptr;
+  return !dfr.empty() ? "k_pass_subset" : fp32 ? pass_name(pass, wide) : "k_mxp_subset";
 }
 
 void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
@@ -835,6 +866,10 @@ void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
   if (!sep.empty())
     run(sep_final ? "k_sep_final" : "k_sep_pass", [&] {
       launch_sep_pass(jobs, d_sep, (int)sep.size(), sep_blocks, sep_final, sep_steps, s);
+    });
+  if (!dfr.empty())
+    run("k_pass_subset", [&] {
+      launch_pass_defer(jobs, d_dfr, (int)dfr.size(), dfr_blocks, dfr_spots, false, dfr_head, s);
     });
   if (!pass.empty())
     run(pass_name(pass, {}),
@@ -847,7 +882,9 @@ void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
     run("k_backprop_phi",
         [&] { launch_backprop_batch(jobs, d_back, (int)back.size(), back_blocks, s); });
   if (!mxp.empty())
-    run("k_mxp_subset", [&] { launch_pass_mx(jobs, d_mxp, (int)mxp.size(), mxp_blocks, 1, s); });
+    run("k_mxp_subset", [&] {
+      launch_pass_defer(jobs, d_mxp, (int)mxp.size(), mxp_blocks, kBlock, true, mxp_head, s);
+    });
   if (!mxw.empty())
     run("k_mxp_subset",
         [&] { launch_pass_mx(jobs, d_mxw, (int)mxw.size(), mxw_blocks, mxw_units, s); });
@@ -861,8 +898,23 @@ void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
 
 // ------------------------------------------------------------------- batch --
 
-hg_status Batch::build(const JobSpec* specs, int count, const TuneParams& tp,
+namespace {
+// Whether a single job's compressed passes can run chained: FP32 two-sincos
+// passes of one hologram, at least two of them, on a grid resident at once.
+bool chain_fits(const JobSpec& s, const TuneParams& tp) {
+  if (!job_compressed(s) || s.precision == HG_PREC_MIXED || s.N > kChainMaxSpots ||
+      s.iterations < 3 || (tp.pass_form == 1 && pass_e_width(s.N) > 0))
+    return false;
+  const int32_t P = s.pupil_n > 0 ? s.pupil_n : s.W * s.H;
+  const PassPlan p = plan_pass((int32_t)std::ceil(s.compression * (double)P), tp.subset_block_cap);
+  return p.blocks <= pass_chain_capacity(pass_units_per_wave(s.N));
+}
+}  // namespace
+
+hg_status Batch::build(const JobSpec* specs, int count, const TuneParams& tune,
                        int32_t* status_dev, bool allow_chain) {
+  TuneParams tp = tune;
+  tp.chain_passes = tune.chain_passes && allow_chain && count == 1 && chain_fits(specs[0], tune);
   specs_.assign(specs, specs + count);
   jobs_.assign(count, JobDev{});
   layouts_.resize(count);
@@ -916,33 +968,30 @@ hg_status Batch::build(const JobSpec* specs, int count, const TuneParams& tp,
   // chained launch of a single FP32 job's compressed passes
   chain_descs_.clear();
   chain_rounds_ = 0;
-  if (allow_chain && tp.chain_passes && count == 1) {
+  if (tp.chain_passes) {
     const JobDev& j = jobs_[0];
     const int passes = j.iterations - 1;  // iterations 1..I-1 are compressed
     const int units = pass_units_per_wave(j.N);
-    if (j.compressed && !j.mixed && !j.shared_e && j.N <= kChainMaxSpots && passes >= 2 &&
-        layouts_[0].plan_sub.blocks <= pass_chain_capacity(units)) {
-      for (int r = 0; r < passes; ++r) {
-        // a chained launch hands the state over inside the launch
-        PassDesc d = rounds_[r].pass.at(0);
-        clear_deferral(d);
-        chain_descs_.push_back(d);
-      }
-      // and the passes after it update in their own tails (the chain's
-      // last pass leaves the state in the spot records); so does the last
-      // compressed pass of the one-launch-per-pass form that stands in when
-      // the cooperative launch is refused
-      if ((size_t)passes < rounds_.size())
-        for (SepDesc& d : rounds_[passes].sep) clear_deferral(d);
-      for (SepDesc& d : final_.sep) clear_deferral(d);
-      for (PassDesc& d : rounds_[passes - 1].pass) {
-        d.defer = 0;
-        d.st_out = nullptr;
-      }
-      chain_rounds_ = passes;
-      chain_blocks_ = layouts_[0].plan_sub.blocks;
-      chain_units_ = units;
+    for (int r = 0; r < passes; ++r) {
+      // a chained launch hands the state over inside the launch
+      PassDesc d = rounds_[r].pass.at(0);
+      clear_deferral(d);
+      chain_descs_.push_back(d);
     }
+    // and the passes after it update in their own tails (the chain's
+    // last pass leaves the state in the spot records); so does the last
+    // compressed pass of the one-launch-per-pass form that stands in when
+    // the cooperative launch is refused
+    if ((size_t)passes < rounds_.size())
+      for (SepDesc& d : rounds_[passes].sep) clear_deferral(d);
+    for (SepDesc& d : final_.sep) clear_deferral(d);
+    for (PassDesc& d : rounds_[passes - 1].pass) {
+      d.defer = 0;
+      d.st_out = nullptr;
+    }
+    chain_rounds_ = passes;
+    chain_blocks_ = layouts_[0].plan_sub.blocks;
+    chain_units_ = units;
   }
   // descriptor tables: [JobDev][JobSlice perm][PrologueSlice][chain passes]
   // [rounds...][final]

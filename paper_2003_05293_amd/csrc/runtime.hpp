@@ -133,6 +133,7 @@ struct TuneParams {
   bool separable_full = true;  // full-grid passes as separable products
   int32_t pass_form = 0;       // 1: shared-exponential compressed passes where N allows
   bool chain_passes = false;   // chained launch of a single job's compressed passes
+                               // (Batch::build drops it where that cannot run)
 };
 
 // Pupil of an hg_optics (validated): the aperture bound q = floor(D^2)
@@ -186,6 +187,11 @@ struct LaunchSet {
   // per-pixel passes in two launches: jobs of one spot unit per wave (and
   // the shared-exponential form) in `pass`, wider jobs in `wide`, so that
   // every job runs in the same kernel form alone and in any batch
+  // (the passes of `deferring` jobs in launches of their own: dfr, FP32, and
+  // mxp, mixed)
+  std::vector<PassDesc> dfr;
+  int dfr_blocks = 0, dfr_spots = 0;
+  PassHead dfr_head, mxp_head;  // of the first pass of each
   std::vector<PassDesc> pass;
   int pass_blocks = 0;
   int e_width = 0;  // widest shared-exponential form among the passes (0: none)
@@ -200,12 +206,13 @@ struct LaunchSet {
   int mx_blocks = 0, mx_steps = 0, mx_full = 0;
   int mx_mode = kMxIterate;
   // compressed passes of mixed-precision jobs (per-pixel, FP16
-  // back-propagation): one unit per wave in mxp, wider jobs in mxw
+  // back-propagation): deferring jobs in mxp, wider jobs in mxw
   std::vector<PassDesc> mxp;
   int mxp_blocks = 0;
   std::vector<PassDesc> mxw;
   int mxw_blocks = 0, mxw_units = 1;
   // device copies, set by stage()
+  const PassDesc* d_dfr = nullptr;
   const PassDesc* d_pass = nullptr;
   const PassDesc* d_wide = nullptr;
   const SepDesc* d_sep = nullptr;
@@ -220,7 +227,7 @@ struct LaunchSet {
   // pixels, no update).
   void add_forward_mx(const JobDev& j, const JobLayout& L, int index);
   bool empty() const {
-    return pass.empty() && wide.empty() && sep.empty() && back.empty() && mx.empty() &&
+    return dfr.empty() && pass.empty() && wide.empty() && sep.empty() && back.empty() && mx.empty() &&
            mxp.empty() && mxw.empty();
   }
   // Timing name of the set's per-pixel pass launch when that is all the set
