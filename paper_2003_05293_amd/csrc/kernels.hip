@@ -475,7 +475,8 @@ __device__ void pass_block(const PassCtx& a, unsigned* grab, bool has_pre = fals
   const int lane = threadIdx.x & 63;
   const int N = a.N;
   const LaneMap lm = lane_map(N);
-  const int g = lane % lm.Lg, r = lane / lm.Lg;
+  const int Lg = 1 << lm.lgL, R = 64 >> lm.lgL, S = 1 << lm.lgS;
+  const int g = lane & (Lg - 1), r = lane >> lm.lgL;
   const SpotRec* __restrict__ sp = a.sp;
   if (threadIdx.x == 0) ndone = nowned = 0;
   constexpr bool lds_recs = CHAIN || PEND;
@@ -484,7 +485,7 @@ __device__ void pass_block(const PassCtx& a, unsigned* grab, bool has_pre = fals
 #pragma unroll
   for (int k = 0; k < MAXU; ++k) {
     const int u = wave + k * kWaves;
-    const int n = (u / lm.S) * lm.Lg + g;
+    const int n = (u >> lm.lgS) * Lg + g;
     cx[k] = cy[k] = cz[k] = 0.f;
     if (u < lm.U && n < N) {
       if (lds_recs) {
@@ -595,14 +596,12 @@ __device__ void pass_block(const PassCtx& a, unsigned* grab, bool has_pre = fals
       if (u < lm.U) red[u][lane] = make_float2(vr[k], vi[k]);
     }
     __syncthreads();
-    for (int idx = threadIdx.x; idx < lm.nch * lm.Lg; idx += kBlock) {
-      const int ch = idx / lm.Lg, gg = idx % lm.Lg;
-      const int n = ch * lm.Lg + gg;
-      if (n >= N) continue;
+    for (int n = threadIdx.x; n < N; n += kBlock) {
+      const int ch = n >> lm.lgL, gg = n & (Lg - 1);
       float2 acc = make_float2(0.f, 0.f);
-      for (int sl = 0; sl < lm.S; ++sl)
-        for (int rr = 0; rr < lm.R; ++rr) {
-          const float2 v = red[ch * lm.S + sl][rr * lm.Lg + gg];
+      for (int sl = 0; sl < S; ++sl)
+        for (int rr = 0; rr < R; ++rr) {
+          const float2 v = red[ch * S + sl][rr * Lg + gg];
           acc.x += v.x;
           acc.y += v.y;
         }

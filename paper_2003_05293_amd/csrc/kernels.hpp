@@ -112,9 +112,31 @@ __host__ __device__ inline int32_t pupil_run(int32_t W, int32_t H, int32_t q, in
   return b >= a ? (int32_t)(b - a + 1) : 0;
 }
 
+// Row of pixel p < 2^26 on a grid of 2 <= W <= 8192 columns: p / W =
+// (p m) >> (32 + sh).  With 2^sh <= W < 2^(sh + 1) and m = ceil(2^(32 + sh) / W)
+// the excess m W - 2^(32 + sh) < W < 2^(sh + 1) times p stays below 2^(32 + sh).
+struct RowDivisor {
+  uint32_t m;
+  int32_t sh;
+};
+inline RowDivisor row_divisor(int32_t W) {
+  RowDivisor r{0u, 0};
+  while ((W >> (r.sh + 1)) != 0) ++r.sh;
+  const uint64_t top = uint64_t(1) << (32 + r.sh);
+  const uint64_t m = (top + (uint64_t)W - 1) / (uint64_t)W;
+  if (m >> 32) {  // W a power of two: half of both
+    r.m = 0x80000000u;
+    r.sh -= 1;
+  } else {
+    r.m = (uint32_t)m;
+  }
+  return r;
+}
+
 // One hologram resident on the device.
 struct JobDev {
   int32_t W, H, N, M;
+  RowDivisor row_div;  // of W
   int32_t P;           // pixels of the pupil Omega (M without an aperture):
                        // the full pass's count and the random order's length
   int32_t ap_q;        // aperture: the pixels with Lx^2 + Ly^2 <= ap_q (-1: all)
@@ -285,7 +307,8 @@ struct PassHead {
   const SpotRec* st = nullptr;              // state before the previous pass's update
   const unsigned long long* tot = nullptr;  // the previous pass's total set (null: no update)
   const int32_t* perm = nullptr;
-  int32_t start = 0, P = 0, count = 0, N = 0, W = 0, H = 0;
+  int32_t start = 0, P = 0, count = 0, N = 0, sub = 1, W = 0, H = 0;
+  RowDivisor row_div{0u, 0};
   int32_t job = 0;                          // index of the job in the launch's table
 };
 void launch_pass_defer(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,

@@ -39,13 +39,18 @@ struct PassStart {
   const SpotRec* st;               // spot state before the previous pass's update
   const unsigned long long* tot;   // the previous pass's total set (null: no update)
   const int32_t* perm;
-  int start, P, count, N, W, H;
+  int start, P, count, N, sub, W, H;
+  uint32_t div_m;                  // row_divisor(W)
+  int div_sh;
 };
 
 __device__ __forceinline__ int32_t window_pixel(const PassStart& h, int q) {
-  int64_t k = (int64_t)h.start + q;
-  if (k >= h.P) k -= h.P;
+  uint32_t k = (uint32_t)h.start + (uint32_t)q;  // below 2 P <= 2^27
+  if (k >= (uint32_t)h.P) k -= (uint32_t)h.P;
   return as_global(h.perm)[k];
+}
+__device__ __forceinline__ PixCoord coord_of(const PassStart& h, int32_t p) {
+  return pixel_coord(p, h.W, h.H, h.div_m, h.div_sh);
 }
 
 // One pass of one job.  MAXU: spot units per wave (1: N <= 256, 2: N <= 512).
@@ -72,12 +77,13 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   const int lane = threadIdx.x & 63;
   const int N = h.N;
   const LaneMap lm = lane_map(N);
-  const int g = lane % lm.Lg, r = lane / lm.Lg;
+  const int Lg = 1 << lm.lgL, R = 64 >> lm.lgL, S = 1 << lm.lgS;
+  const int g = lane & (Lg - 1), r = lane >> lm.lgL;
   float cx[MAXU], cy[MAXU], cz[MAXU];
 #pragma unroll
   for (int k = 0; k < MAXU; ++k) {
     const int u = wave + k * kWaves;
-    const int n = (u / lm.S) * lm.Lg + g;
+    const int n = ((u >> lm.lgS) << lm.lgL) + g;
     cx[k] = cy[k] = cz[k] = 0.f;
     if (u < lm.U && n < N) {
       cx[k] = recs[n].cx;
@@ -85,7 +91,8 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
       cz[k] = recs[n].cz;
     }
   }
-  const int n_lo = (wave * N) / kWaves, n_hi = ((wave + 1) * N) / kWaves;
+  const int n_lo = (int)((unsigned)(wave * N) / kWaves);
+  const int n_hi = (int)((unsigned)((wave + 1) * N) / kWaves);
   const double scale = ldexp(1.0, plan.shift);
   bool first = true;
   int buf = 0;
@@ -96,7 +103,7 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
     for (int st = 0; st < plan.sub; ++st) {
       const int32_t q = (tile * plan.sub + st) * kTile + lane;
       const bool valid = q < h.count;
-      if (!first) c = pixel_coord(valid ? window_pixel(h, q) : 0, h.W, h.H);
+      if (!first) c = coord_of(h, valid ? window_pixel(h, q) : 0);
       first = false;
       if (!valid) c = PixCoord{0.f, 0.f, 0.f, 0};
       sw[buf][wave][lane] =
@@ -149,46 +156,55 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
         acc + (int64_t)(tot_row * kAccReplicas + tile % kAccReplicas) * N * kAccSpotWords;
     for (int x = threadIdx.x; x < 2 * N; x += kBlock) {
       const int n = x >> 1, part = x & 1;
-      const int ch = n / lm.Lg, gg = n % lm.Lg;
+      const int ch = n >> lm.lgL, gg = n & (Lg - 1);
+      const float* row = reinterpret_cast<const float*>(&red[ch << lm.lgS][gg]) + part;
       float s = 0.f;
-      for (int sl = 0; sl < lm.S; ++sl)
-        for (int rr = 0; rr < lm.R; ++rr)
-          s += reinterpret_cast<const float*>(&red[ch * lm.S + sl][rr * lm.Lg + gg])[part];
+      if (R == 1) {
+        for (int sl = 0; sl < S; ++sl) s += row[2 * 64 * sl];
+      } else {
+        for (int sl = 0; sl < S; ++sl)
+          for (int rr = 0; rr < R; ++rr) s += row[2 * (64 * sl + (rr << lm.lgL))];
+      }
       atomicAdd(out + x, (unsigned long long)llrint((double)s * scale));
     }
     if (tile + plan.blocks < plan.tiles) __syncthreads();  // red is rewritten
   }
 }
 
-// One round of deferring passes.  With one pass in the launch (ndesc == 1)
-// its start comes as kernel arguments, the first sixteen dwords of which are
-// in registers when the wave begins: the reads of the state, the totals and
-// the pixel order then start without waiting for the descriptor and, after
-// it, the job record (two memory round trips), and `jobs` is that job.
+// One round of deferring passes.  With one pass in the launch its start comes
+// as kernel arguments, the first fourteen dwords of which are in registers
+// when the wave begins: the reads of the state, the totals and the pixel
+// order then start without waiting for the descriptor and, after it, the job
+// record (two memory round trips), and `jobs` is that job.  nss: N, the shift
+// of the row division from bit 16, parts per tile from bit 21; wh: W, H from
+// bit 15, bit 31 set with several passes (then only descs and jobs count and
+// `start` is the number of passes).
 template <int MAXU, bool MX>
 __global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
     const SpotRec* st, const unsigned long long* tot, const int32_t* perm, int32_t start, int32_t P,
-    int32_t count, int32_t N, uint32_t WH, int32_t ndesc, const PassDesc* __restrict__ descs,
+    int32_t count, uint32_t nss, uint32_t wh, uint32_t div_m, const PassDesc* __restrict__ descs,
     const JobDev* __restrict__ jobs) {
   constexpr int kMaxN = MAXU > 1 ? kDeferMaxSpots : kBlock;
   __shared__ SpotRec recs[kMaxN];
-  PassStart h{st, tot, perm, start, P, count, N, (int)(WH & 0xffffu), (int)(WH >> 16)};
+  PassStart h{st, tot, perm, start, P, count, (int)(nss & 0xffffu), (int)(nss >> 21),
+              (int)(wh & 0x7fffu), (int)(wh >> 15 & 0x7fffu), div_m, (int)(nss >> 16 & 31u)};
   const PassDesc* dp = descs;
   const JobDev* jp = jobs;
   int lb = blockIdx.x;
-  if (ndesc > 1) {
-    dp += find_desc(descs, ndesc, blockIdx.x);
+  if (wh >> 31) {  // several passes: `start` is their number
+    dp += find_desc(descs, start, blockIdx.x);
     jp += dp->job;
     lb -= dp->block_begin;
     h = PassStart{dp->pending ? dp->st_in : jp->sp,
                   dp->pending ? jp->acc + (int64_t)dp->prev_row * kAccReplicas * jp->N * kAccSpotWords
                               : nullptr,
-                  dp->ps.perm, (int)dp->ps.start, dp->ps.M, dp->ps.count, jp->N, jp->W, jp->H};
+                  dp->ps.perm, (int)dp->ps.start, dp->ps.M, dp->ps.count, jp->N, dp->plan.sub,
+                  jp->W, jp->H, jp->row_div.m, jp->row_div.sh};
   }
   const PassDesc& d = *dp;
   const JobDev& jb = *jp;
   // the pixel of this lane in the block's first 64, requested with the state
-  const int q0 = lb * d.plan.sub * kTile + (int)(threadIdx.x & 63);
+  const int q0 = lb * h.sub * kTile + (int)(threadIdx.x & 63);
   const int32_t p0 = q0 < h.count ? window_pixel(h, q0) : 0;
   // the updating waves: another pair of the four SIMDs for each of the blocks
   // that share a compute unit (blocks 256 apart)
@@ -197,10 +213,10 @@ __global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
   if (h.tot) {
     PendingState<kMaxN> ps;
     ps.load(h.st, h.tot, h.N, vt);
-    c = pixel_coord(p0, h.W, h.H);
+    c = coord_of(h, p0);
     ps.apply(jb, d, h.N, lb == 0, vt, recs, nullptr);
   } else {
-    c = pixel_coord(p0, h.W, h.H);
+    c = coord_of(h, p0);
     const HG_GLOBAL float* src = as_global(reinterpret_cast<const float*>(h.st));
     float* dst = reinterpret_cast<float*>(recs);
     for (int k = threadIdx.x; k < (int)(sizeof(SpotRec) / sizeof(float)) * h.N; k += kBlock)
@@ -217,10 +233,12 @@ void launch_pass_defer(const JobDev* jobs, const PassDesc* descs, int ndesc, int
   if (ndesc <= 0 || total_blocks <= 0) return;
   const dim3 grid(total_blocks), block(kBlock);
   const JobDev* j = ndesc == 1 ? jobs + head.job : jobs;
-  const uint32_t WH = (uint32_t)head.W | ((uint32_t)head.H << 16);
+  const uint32_t nss = (uint32_t)head.N | ((uint32_t)head.row_div.sh << 16) | ((uint32_t)head.sub << 21);
+  const uint32_t wh = (uint32_t)head.W | ((uint32_t)head.H << 15) | (ndesc > 1 ? 0x80000000u : 0u);
+  const int32_t start = ndesc > 1 ? ndesc : head.start;
 #define HG_LAUNCH(U, M)                                                                          \
   hipLaunchKernelGGL((k_pass_defer<U, M>), grid, block, 0, s, head.st, head.tot, head.perm,      \
-                     head.start, head.P, head.count, head.N, WH, ndesc, descs, j)
+                     start, head.P, head.count, nss, wh, head.row_div.m, descs, j)
   if (mixed) HG_LAUNCH(1, true);
   else if (max_spots <= kBlock) HG_LAUNCH(1, false);
   else HG_LAUNCH(2, false);

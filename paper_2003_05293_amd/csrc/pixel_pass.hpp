@@ -23,9 +23,7 @@ struct PixCoord {
   int32_t Qi;
 };
 
-__device__ __forceinline__ PixCoord pixel_coord(int32_t p, int W, int H) {
-  const int32_t j = p / W;
-  const int32_t i = p - j * W;
+__device__ __forceinline__ PixCoord pixel_coord_ij(int32_t i, int32_t j, int W, int H) {
   const int32_t lx = 2 * i - (W - 1);
   const int32_t ly = 2 * j - (H - 1);
   PixCoord c;
@@ -34,6 +32,16 @@ __device__ __forceinline__ PixCoord pixel_coord(int32_t p, int W, int H) {
   c.Qi = lx * lx + ly * ly;
   c.Q = (float)c.Qi;
   return c;
+}
+__device__ __forceinline__ PixCoord pixel_coord(int32_t p, int W, int H) {
+  const int32_t j = p / W;
+  return pixel_coord_ij(p - j * W, j, W, H);
+}
+// The same with the row from a multiplication: j = (p m) >> (32 + sh), m and
+// sh from row_divisor(W), exact for p < 2^26 (W, H <= 8192).
+__device__ __forceinline__ PixCoord pixel_coord(int32_t p, int W, int H, uint32_t m, int sh) {
+  const int32_t j = (int32_t)(__umulhi((uint32_t)p, m) >> sh);
+  return pixel_coord_ij(p - j * W, j, W, H);
 }
 
 // The same sum with the spot records in LDS (pending and chained
@@ -141,23 +149,22 @@ __device__ __forceinline__ void forward_term(float cx, float cy, float cz, const
   vi = fmaf(ui, cs, fmaf(-a.w, sn, vi));
 }
 
-// Spot-lane layout of phase 2 for N spots.
+// Spot-lane layout of phase 2 for N spots.  Every size but the chunk count
+// is a power of two, kept as its logarithm.
 struct LaneMap {
-  int Lg;   // lanes per spot group (8, 16, 32 or 64)
-  int R;    // replicas per wave = 64 / Lg
-  int nch;  // spot chunks = ceil(N / Lg)
-  int S;    // pixel slices per chunk
-  int U;    // units = nch * S
+  int lgL;  // lanes per spot group 2^lgL (8, 16, 32 or 64); replicas 64 >> lgL
+  int nch;  // spot chunks = ceil(N / lanes)
+  int lgS;  // pixel slices per chunk 2^lgS (1, 2 or 4)
+  int U;    // units = chunks * slices
 };
 
 __host__ __device__ inline LaneMap lane_map(int N) {
   LaneMap m;
-  const int n = N < 64 ? N : 64;
-  m.Lg = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 32 : 64;
-  m.R = 64 / m.Lg;
-  m.nch = (N + m.Lg - 1) / m.Lg;
-  m.S = m.nch >= kWaves ? 1 : kWaves / m.nch;
-  m.U = m.nch * m.S;
+  m.lgL = N <= 8 ? 3 : N <= 16 ? 4 : N <= 32 ? 5 : 6;
+  m.nch = (N + (1 << m.lgL) - 1) >> m.lgL;
+  static_assert(kWaves == 4, "slices of four waves");
+  m.lgS = m.nch == 1 ? 2 : m.nch == 2 ? 1 : 0;
+  m.U = m.nch << m.lgS;
   return m;
 }
 
@@ -169,11 +176,12 @@ template <bool PAIRS>
 __device__ __forceinline__ void forward_unit(const LaneMap& lm, int u, int r, float cx, float cy,
                                              float cz, const float4* px, const float* pui,
                                              float& vr, float& vi) {
-  const int sl = u % lm.S;
-  const int j0 = (sl * kTile) / lm.S + r, j1 = ((sl + 1) * kTile) / lm.S;
+  static_assert(kTile == 64, "slices of a 64-pixel tile");
+  const int sl = u & ((1 << lm.lgS) - 1), R = 64 >> lm.lgL;
+  const int j0 = (sl << (6 - lm.lgS)) + r, j1 = (sl + 1) << (6 - lm.lgS);
   float ar = vr, ai = vi, br = 0.f, bi = 0.f;
   int j = j0;
-  if (PAIRS && lm.R == 1) {
+  if (PAIRS && R == 1) {
     // one replica (r = 0): the pixel loop is uniform across the
     // wave, so its counter and the LDS addresses stay scalar
     int ju = __builtin_amdgcn_readfirstlane(j0);
@@ -188,17 +196,17 @@ __device__ __forceinline__ void forward_unit(const LaneMap& lm, int u, int r, fl
     }
     j = ju;
   } else if (PAIRS) {
-    for (; j + 3 * lm.R < j1; j += 4 * lm.R) {
-      const float4 p0 = px[j], p1 = px[j + lm.R], p2 = px[j + 2 * lm.R], p3 = px[j + 3 * lm.R];
-      const float u0 = pui[j], u1 = pui[j + lm.R], u2 = pui[j + 2 * lm.R],
-                  u3 = pui[j + 3 * lm.R];
+    for (; j + 3 * R < j1; j += 4 * R) {
+      const float4 p0 = px[j], p1 = px[j + R], p2 = px[j + 2 * R], p3 = px[j + 3 * R];
+      const float u0 = pui[j], u1 = pui[j + R], u2 = pui[j + 2 * R],
+                  u3 = pui[j + 3 * R];
       forward_term(cx, cy, cz, p0, u0, ar, ai);
       forward_term(cx, cy, cz, p1, u1, br, bi);
       forward_term(cx, cy, cz, p2, u2, ar, ai);
       forward_term(cx, cy, cz, p3, u3, br, bi);
     }
   }
-  for (; j < j1; j += lm.R) forward_term(cx, cy, cz, px[j], pui[j], ar, ai);
+  for (; j < j1; j += R) forward_term(cx, cy, cz, px[j], pui[j], ar, ai);
   vr = ar + br;
   vi = ai + bi;
 }

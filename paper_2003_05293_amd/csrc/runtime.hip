@@ -425,6 +425,7 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
   j.H = s.H;
   j.N = s.N;
   j.M = s.W * s.H;
+  j.row_div = row_divisor(s.W);
   j.P = s.pupil_n > 0 ? s.pupil_n : j.M;
   j.ap_q = s.ap_q;
   j.ill_a = (float)illumination_exponent(s.pitch_mm, s.waist_mm);
@@ -451,8 +452,9 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
   L.separable = !j.mixed && tp.separable_full && !s.full_direct;
   // compressed passes without an update of their own, where every pass up to
   // the final hologram takes deferred updates (a chained launch hands its
-  // updates over inside the launch instead)
-  j.deferring = (j.compressed && s.phi && !tp.chain_passes && !j.shared_e &&
+  // updates over inside the launch instead; a grid of one column has no
+  // row divisor)
+  j.deferring = (j.compressed && s.phi && s.W >= 2 && !tp.chain_passes && !j.shared_e &&
                  (j.mixed ? pass_units_per_wave(s.N) == 1 : L.separable && s.N <= kDeferMaxSpots))
                     ? 1
                     : 0;
@@ -724,6 +726,8 @@ PassHead pass_head(const JobDev& j, const PassDesc& d) {
   h.P = d.ps.M;
   h.count = d.ps.count;
   h.N = j.N;
+  h.sub = d.plan.sub;
+  h.row_div = j.row_div;
   h.W = j.W;
   h.H = j.H;
   h.job = d.job;
