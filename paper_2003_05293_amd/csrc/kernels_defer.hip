@@ -94,8 +94,15 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   const int n_lo = (int)((unsigned)(wave * N) / kWaves);
   const int n_hi = (int)((unsigned)((wave + 1) * N) / kWaves);
   const double scale = ldexp(1.0, plan.shift);
-  bool first = true;
+  // this thread's components of the tiles' sums (x = threadIdx.x + i kBlock)
+  constexpr int kSums = 2 * MAXU;  // 2 N <= kSums kBlock
+  unsigned long long sums[kSums];
+#pragma unroll
+  for (int i = 0; i < kSums; ++i) sums[i] = 0ull;
+  // the pixel index of the next 64 pixels is requested before the arithmetic
+  // of the current ones
   int buf = 0;
+  int32_t next = 0;
   for (int tile = lb; tile < plan.tiles; tile += plan.blocks) {
     float vr[MAXU], vi[MAXU];
 #pragma unroll
@@ -103,9 +110,10 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
     for (int st = 0; st < plan.sub; ++st) {
       const int32_t q = (tile * plan.sub + st) * kTile + lane;
       const bool valid = q < h.count;
-      if (!first) c = coord_of(h, valid ? window_pixel(h, q) : 0);
-      first = false;
+      if (tile != lb || st != 0) c = coord_of(h, next);
       if (!valid) c = PixCoord{0.f, 0.f, 0.f, 0};
+      const int32_t qn = (st + 1 < plan.sub ? q : ((tile + plan.blocks) * plan.sub - 1) * kTile + lane) + kTile;
+      next = qn < h.count ? window_pixel(h, qn) : 0;
       sw[buf][wave][lane] =
           MX ? backprop_field_mx_lds(recs, n_lo, n_hi, c) : backprop_field_lds(recs, n_lo, n_hi, c);
       __syncthreads();
@@ -152,9 +160,10 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
       if (u < lm.U) red[u][lane] = make_float2(vr[k], vi[k]);
     }
     __syncthreads();
-    unsigned long long* out =
-        acc + (int64_t)(tot_row * kAccReplicas + tile % kAccReplicas) * N * kAccSpotWords;
-    for (int x = threadIdx.x; x < 2 * N; x += kBlock) {
+#pragma unroll
+    for (int i = 0; i < kSums; ++i) {
+      const int x = threadIdx.x + i * kBlock;
+      if (x >= 2 * N) break;
       const int n = x >> 1, part = x & 1;
       const int ch = n >> lm.lgL, gg = n & (Lg - 1);
       const float* row = reinterpret_cast<const float*>(&red[ch << lm.lgS][gg]) + part;
@@ -165,9 +174,16 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
         for (int sl = 0; sl < S; ++sl)
           for (int rr = 0; rr < R; ++rr) s += row[2 * (64 * sl + (rr << lm.lgL))];
       }
-      atomicAdd(out + x, (unsigned long long)llrint((double)s * scale));
+      sums[i] += (unsigned long long)llrint((double)s * scale);
     }
     if (tile + plan.blocks < plan.tiles) __syncthreads();  // red is rewritten
+  }
+  unsigned long long* out =
+      acc + (int64_t)(tot_row * kAccReplicas + lb % kAccReplicas) * N * kAccSpotWords;
+#pragma unroll
+  for (int i = 0; i < kSums; ++i) {
+    const int x = threadIdx.x + i * kBlock;
+    if (x < 2 * N) atomicAdd(out + x, sums[i]);
   }
 }
 
@@ -184,6 +200,9 @@ __global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
     const SpotRec* st, const unsigned long long* tot, const int32_t* perm, int32_t start, int32_t P,
     int32_t count, uint32_t nss, uint32_t wh, uint32_t div_m, const PassDesc* __restrict__ descs,
     const JobDev* __restrict__ jobs) {
+  // the start runs ahead of the arithmetic of the blocks that share the SIMD:
+  // a block that is late with its update is late at the end
+  __builtin_amdgcn_s_setprio(3);
   constexpr int kMaxN = MAXU > 1 ? kDeferMaxSpots : kBlock;
   __shared__ SpotRec recs[kMaxN];
   PassStart h{st, tot, perm, start, P, count, (int)(nss & 0xffffu), (int)(nss >> 21),
@@ -223,6 +242,7 @@ __global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
       dst[k] = src[k];
     __syncthreads();
   }
+  __builtin_amdgcn_s_setprio(0);
   defer_tiles<MAXU, MX>(h, d.plan, lb, d.tot_row, jb.acc, jb.ill_a, recs, c);
 }
 

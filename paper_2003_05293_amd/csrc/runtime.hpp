@@ -237,6 +237,8 @@ struct LaunchSet {
   // Copies the descriptors into host staging at `host` and points the
   // device copies at `dev` (same offsets); returns the bytes used.
   size_t stage(char* host, char* dev);
+  // Several tiles per block where the launch has many blocks (stage() does it).
+  void spread_tiles();
   // Launches the set's kernels.  `capture`: no timing.
   void launch(const JobDev* jobs, hipStream_t s, bool capture) const;
 };
