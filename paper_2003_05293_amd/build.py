@@ -22,7 +22,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libhg.so")
 MICROBENCH = ("bench_alu", "bench_launch")
-SOURCES = ["kernels.hip", "kernels_defer.hip", "kernels_mx.hip", "kernels_sep.hip", "runtime.hip", "api.hip", "engine.hip"]
+SOURCES = ["kernels.hip", "kernels_defer.hip", "kernels_metrics.hip", "kernels_mx.hip", "kernels_sep.hip", "runtime.hip", "api.hip", "engine.hip"]
 ARCH = "gfx950"
 
 # Kernel arguments preloaded into SGPRs (gfx950 loads the first 16 dwords

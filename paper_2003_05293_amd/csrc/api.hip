@@ -26,6 +26,16 @@ namespace {
 
 using hg::set_error;
 
+// The error that a device status word stands for.
+hg_status status_error(int32_t st) {
+  if (st == 0) return HG_OK;
+  if (st == HG_EINVAL)
+    return set_error(HG_EINVAL, "device-resident spot values were not finite or an amplitude "
+                                "was not positive (in this or an earlier call on this stream)");
+  return set_error(HG_ENUMERIC, "a spot field came out zero or not finite (in this or an "
+                                "earlier call on this stream)");
+}
+
 // Scratch of one (device, stream).  Calls on the same stream run in stream
 // order, so the buffers are reused from call to call.  `status` is sticky:
 // kernels raise it, blocking calls report and clear it.
@@ -36,8 +46,9 @@ struct Workspace {
   hg::Batch batch;
   hg::DevBuf<int32_t> status;
   hg::DevBuf<double> raw;             // metrics: spot inputs; theta0 output
-  hg::DevBuf<double2> Ex, Ey, mpart, V;
+  hg::DevBuf<double2> Ex, Ey, mpart;
   hg::Staging staging;
+  hg::Staging results;                // metrics: what the GPU writes for the host
 
   hg_status init_status() {
     if (status.p) return HG_OK;
@@ -52,11 +63,7 @@ struct Workspace {
     HG_HIP(hipMemcpy(&st, status.p, sizeof(int32_t), hipMemcpyDeviceToHost));
     if (st == 0) return HG_OK;
     HG_HIP(hipMemset(status.p, 0, sizeof(int32_t)));
-    if (st == HG_EINVAL)
-      return set_error(HG_EINVAL, "device-resident spot values were not finite or an amplitude "
-                                  "was not positive (in this or an earlier call on this stream)");
-    return set_error(HG_ENUMERIC, "a spot field came out zero or not finite (in this or an "
-                                  "earlier call on this stream)");
+    return status_error(st);
   }
 
   void release() {
@@ -66,8 +73,8 @@ struct Workspace {
     Ex.release();
     Ey.release();
     mpart.release();
-    V.release();
     staging.release();
+    results.release();
   }
 };
 
@@ -405,35 +412,38 @@ hg_status hg_metrics(const hg_grid* grid, const hg_optics* optics, const hg_spot
   a.pitch_mm = grid->pitch_mm;
   a.lambda_mm = optics->lambda_mm;
   a.focal_mm = optics->focal_mm;
-  HG_TRY(ws->Ex.reserve((size_t)grid->W * N));
-  HG_TRY(ws->Ey.reserve((size_t)grid->H * N));
-  const int nblk = hg::metric_blocks(grid->H);
-  HG_TRY(ws->mpart.reserve((size_t)nblk * N));
-  HG_TRY(ws->V.reserve(N));
+  const hg::MetricPlan plan = hg::plan_metrics(grid->W, grid->H);
+  const size_t Np = (size_t)hg::metric_spots(N);
+  HG_TRY(ws->Ex.reserve((size_t)hg::metric_cols(grid->W) * Np));
+  HG_TRY(ws->Ey.reserve((size_t)hg::metric_rows(grid->H) * Np));
+  HG_TRY(ws->mpart.reserve((size_t)plan.blocks() * N));
+  // the results come back in pinned host memory: N fields, then the status
+  HG_TRY(ws->results.acquire(sizeof(double2) * N + sizeof(int32_t)));
+  double2* V = reinterpret_cast<double2*>(ws->results.p);
+  int32_t* status = reinterpret_cast<int32_t*>(V + N);
   hg::launch_metric_tables(a, in, ws->Ex.p, ws->Ey.p, ws->stream);
   // the pupil: V* is the mean over Omega of A e^{i(Phi - phi_n)}
   const int32_t ap_q = hg::aperture_bound(optics);
   const double ill_a = hg::illumination_exponent(grid->pitch_mm, optics->waist_mm);
   const int64_t P = hg::pupil_count(grid->W, grid->H, ap_q);
-  hg::launch_metric_rows(ws->Ex.p, ws->Ey.p, N, grid->W, grid->H, phi_dev, ap_q, ill_a,
-                         ws->mpart.p, ws->stream);
-  hg::launch_metric_reduce(ws->mpart.p, nblk, N, 1.0 / (double)P, ws->V.p, ws->stream);
+  hg::launch_metric_tiles(plan, ws->Ex.p, ws->Ey.p, N, grid->W, grid->H, phi_dev, ap_q, ill_a,
+                          ws->mpart.p, ws->stream);
+  hg::launch_metric_reduce(ws->mpart.p, plan.blocks(), N, 1.0 / (double)P, V, ws->status.p, status,
+                           ws->stream);
   HG_TRY(check_launch());
-  std::vector<double> V(2 * (size_t)N);
-  HG_HIP(hipMemcpyAsync(V.data(), ws->V.p, sizeof(double2) * N, hipMemcpyDeviceToHost,
-                        ws->stream));
+  // the fraction of the power on the SLM, mean_Omega(A^2), while the GPU works
+  const double power = hg::pupil_power(grid->W, grid->H, ap_q, ill_a);
   HG_HIP(hipStreamSynchronize(ws->stream));
-  HG_TRY(ws->take_status());
+  HG_TRY(status_error(*status));
   double sum = 0.0, lo = INFINITY, hi = -INFINITY;
   for (int n = 0; n < N; ++n) {
-    const double I = V[2 * n] * V[2 * n] + V[2 * n + 1] * V[2 * n + 1];
+    const double I = V[n].x * V[n].x + V[n].y * V[n].y;
     if (intensities) intensities[n] = I;
     sum += I;
     lo = I < lo ? I : lo;
     hi = I > hi ? I : hi;
   }
-  // the fraction of the power on the SLM, mean_Omega(A^2), in the spots
-  *e = sum / hg::pupil_power(grid->W, grid->H, ap_q, ill_a);
+  *e = sum / power;
   *u = (hi + lo) > 0.0 ? 1.0 - (hi - lo) / (hi + lo) : 0.0;
   return HG_OK;
 }

@@ -998,101 +998,6 @@ __global__ __launch_bounds__(kGrayThreads) void k_phase_to_gray(const float* __r
     store_gray(gray, p, bits, gray_level(as_global(phi)[p], lut, levels));
 }
 
-// -------------------------------------------------------------- metrics ---
-
-// FP64 separable factors of e^{-i phi_n}: eq. (2) splits into a part in x'
-// and a part in y', so e^{-i phi_n(i,j)} = Ex[i][n] * Ey[j][n].
-__global__ void k_metric_tables(SetupArgs a, SpotPtrs in, double2* __restrict__ Ex,
-                                double2* __restrict__ Ey) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int N = a.N;
-  const int64_t nx = (int64_t)a.W * N, ny = (int64_t)a.H * N;
-  if (k >= nx + ny) return;
-  const bool is_x = k < nx;
-  const int64_t kk = is_x ? k : k - nx;
-  const int pix = (int)(kk / N);
-  const int n = (int)(kk % N);
-  const int len = is_x ? a.W : a.H;
-  const double off = ((double)pix - 0.5 * (double)(len - 1)) * a.pitch_mm;
-  const double lat = is_x ? in.x[n] : in.y[n];
-  const double z = in.z[n];
-  const double lf = a.lambda_mm * a.focal_mm;
-  const double lf2 = lf * a.focal_mm;
-  double t = lat * off / lf + z * off * off / lf2;  // turns
-  t -= rint(t);
-  double s, c;
-  sincospi(2.0 * t, &s, &c);
-  (is_x ? Ex : Ey)[kk] = make_double2(c, -s);
-}
-
-constexpr int kMetricRows = 4;
-constexpr int kMetricThreads = 128;
-constexpr int kMetricCols = 512;
-
-// V*_n partial over kMetricRows rows: sum_j Ey[j][n] * sum_i e^{i Phi(i,j)} Ex[i][n].
-// With a pupil, e^{i Phi} is weighted by A = exp(-Q ill_a) and by 0 outside
-// the aperture (Q = Lx^2 + Ly^2 > ap_q, ap_q >= 0).
-__global__ __launch_bounds__(kMetricThreads) void k_metric_rows(
-    const double2* __restrict__ Ex, const double2* __restrict__ Ey, int N, int W, int H,
-    const float* __restrict__ phi, int32_t ap_q, double ill_a, double2* __restrict__ partial) {
-  __shared__ double2 u[kMetricCols];
-  const int j0 = blockIdx.x * kMetricRows;
-  for (int n0 = 0; n0 < N; n0 += kMetricThreads) {
-    const int n = n0 + threadIdx.x;
-    double are = 0.0, aim = 0.0;
-    for (int r = 0; r < kMetricRows; ++r) {
-      const int j = j0 + r;
-      if (j >= H) break;
-      double rre = 0.0, rim = 0.0;
-      for (int i0 = 0; i0 < W; i0 += kMetricCols) {
-        const int cols = min(kMetricCols, W - i0);
-        __syncthreads();
-        for (int k = threadIdx.x; k < cols; k += kMetricThreads) {
-          double s, c;
-          sincos((double)phi[(int64_t)j * W + i0 + k], &s, &c);
-          if (ap_q >= 0 || ill_a > 0.0) {
-            const int64_t lx = 2 * (int64_t)(i0 + k) - (W - 1), ly = 2 * (int64_t)j - (H - 1);
-            const int64_t Q = lx * lx + ly * ly;
-            const double wt = (ap_q >= 0 && Q > ap_q) ? 0.0 : (ill_a > 0.0 ? exp(-(double)Q * ill_a) : 1.0);
-            c *= wt;
-            s *= wt;
-          }
-          u[k] = make_double2(c, s);
-        }
-        __syncthreads();
-        if (n < N) {
-          for (int k = 0; k < cols; ++k) {
-            const double2 e = Ex[(int64_t)(i0 + k) * N + n];
-            const double2 v = u[k];
-            rre = fma(v.x, e.x, fma(-v.y, e.y, rre));
-            rim = fma(v.x, e.y, fma(v.y, e.x, rim));
-          }
-        }
-      }
-      if (n < N) {
-        const double2 e = Ey[(int64_t)j * N + n];
-        are = fma(rre, e.x, fma(-rim, e.y, are));
-        aim = fma(rre, e.y, fma(rim, e.x, aim));
-      }
-    }
-    if (n < N) partial[(int64_t)blockIdx.x * N + n] = make_double2(are, aim);
-  }
-}
-
-__global__ void k_metric_reduce(const double2* __restrict__ partial, int nblk, int N,
-                                double inv_count, double2* __restrict__ V) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  double re = 0.0, im = 0.0;
-  for (int b = 0; b < nblk; ++b) {
-    const double2 v = partial[(int64_t)b * N + n];
-    re += v.x;
-    im += v.y;
-  }
-  V[n] = make_double2(re * inv_count, im * inv_count);
-}
-
-
 }  // namespace
 
 // ------------------------------------------------------------ launchers ---
@@ -1246,34 +1151,12 @@ void launch_backprop_batch(const JobDev* jobs, const BackDesc* descs, int ndesc,
                      ndesc);
 }
 
-void launch_metric_tables(const SetupArgs& a, const SpotPtrs& in, double2* Ex, double2* Ey,
-                          hipStream_t s) {
-  const int64_t total = (int64_t)(a.W + a.H) * a.N;
-  hipLaunchKernelGGL(k_metric_tables, dim3(ceil_div(total, 256)), dim3(256), 0, s, a, in, Ex,
-                     Ey);
-}
-
-int metric_blocks(int H) { return ceil_div(H, kMetricRows); }
-
 void launch_phase_to_gray(const float* phi, int64_t count, const uint16_t* lut, int levels,
                           int bits, void* gray, hipStream_t s) {
   if (count <= 0) return;
   const int64_t blocks = ceil_div(count, (int64_t)4 * kGrayThreads);
   hipLaunchKernelGGL(k_phase_to_gray, dim3((unsigned)blocks), dim3(kGrayThreads), 0, s, phi,
                      count, lut, levels, bits, gray);
-}
-
-void launch_metric_rows(const double2* Ex, const double2* Ey, int N, int W, int H,
-                        const float* phi, int32_t ap_q, double ill_a, double2* partial,
-                        hipStream_t s) {
-  hipLaunchKernelGGL(k_metric_rows, dim3(metric_blocks(H)), dim3(kMetricThreads), 0, s, Ex, Ey,
-                     N, W, H, phi, ap_q, ill_a, partial);
-}
-
-void launch_metric_reduce(const double2* partial, int nblk, int N, double inv_count,
-                          double2* V_out, hipStream_t s) {
-  hipLaunchKernelGGL(k_metric_reduce, dim3(ceil_div(N, 128)), dim3(128), 0, s, partial, nblk, N,
-                     inv_count, V_out);
 }
 
 }  // namespace hg

@@ -430,14 +430,31 @@ struct SetupArgs {
   int32_t W, H;
   double pitch_mm, lambda_mm, focal_mm;
 };
+// Padded sizes of the factor tables Ex [metric_cols(W)][metric_spots(N)] and
+// Ey [metric_rows(H)][metric_spots(N)].
+constexpr int kMetricRows = 64;  // rows of a block (16 per wave)
+constexpr int kMetricCols = 60;  // columns whose u a block holds at once (60 KiB)
+__host__ __device__ inline int metric_spots(int N) { return (N + 15) / 16 * 16; }
+__host__ __device__ inline int metric_cols(int W) { return (W + 3) / 4 * 4; }
+__host__ __device__ inline int metric_rows(int H) {
+  return (H + kMetricRows - 1) / kMetricRows * kMetricRows;
+}
+struct MetricPlan {
+  int row_groups;  // blocks along the rows
+  int splits;      // and along the columns, cols (a multiple of 4) each
+  int cols;
+  int chunk;       // columns held at once
+  int blocks() const { return row_groups * splits; }
+};
+MetricPlan plan_metrics(int W, int H);
 void launch_metric_tables(const SetupArgs& a, const SpotPtrs& in, double2* Ex, double2* Ey,
                           hipStream_t s);
-int metric_blocks(int H);
-// ap_q, ill_a: the pupil (JobDev), ill_a here in FP64.
-void launch_metric_rows(const double2* Ex, const double2* Ey, int N, int W, int H,
-                        const float* phi, int32_t ap_q, double ill_a, double2* partial,
-                        hipStream_t s);
+// partial: [p.blocks()][N].  ap_q, ill_a: the pupil (JobDev), ill_a here in FP64.
+void launch_metric_tiles(const MetricPlan& p, const double2* Ex, const double2* Ey, int N, int W,
+                         int H, const float* phi, int32_t ap_q, double ill_a, double2* partial,
+                         hipStream_t s);
+// V_host, status_host: pinned host memory; status: the sticky device status.
 void launch_metric_reduce(const double2* partial, int nblk, int N, double inv_count,
-                          double2* V_out, hipStream_t s);
+                          double2* V_host, int32_t* status, int32_t* status_host, hipStream_t s);
 
 }  // namespace hg

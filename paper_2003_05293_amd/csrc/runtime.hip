@@ -110,11 +110,13 @@ double illumination_exponent(double pitch_mm, double waist_mm) {
 
 double pupil_power(int32_t W, int32_t H, int32_t q, double ill_a) {
   if (!(ill_a > 0.0)) return 1.0;
-  // A^2 = exp(-2 a Lx^2) exp(-2 a Ly^2), summed over each row's run
-  std::vector<double> ex((size_t)W);
+  // A^2 = exp(-2 a Lx^2) exp(-2 a Ly^2), summed over each row's run of
+  // columns as a difference of prefix sums (a few ulp; the sum over every
+  // pixel took the host 1.3 ms at 1152^2)
+  std::vector<double> ex((size_t)W + 1, 0.0);
   for (int32_t i = 0; i < W; ++i) {
     const double lx = 2.0 * i - (W - 1);
-    ex[(size_t)i] = std::exp(-2.0 * ill_a * lx * lx);
+    ex[(size_t)i + 1] = ex[(size_t)i] + std::exp(-2.0 * ill_a * lx * lx);
   }
   double total = 0.0;
   int64_t count = 0;
@@ -123,9 +125,7 @@ double pupil_power(int32_t W, int32_t H, int32_t q, double ill_a) {
     const int32_t c = pupil_run(W, H, q, j, &i0, &i1);
     if (c == 0) continue;
     const double ly = 2.0 * j - (H - 1);
-    double row = 0.0;
-    for (int32_t i = i0; i <= i1; ++i) row += ex[(size_t)i];
-    total += row * std::exp(-2.0 * ill_a * ly * ly);
+    total += (ex[(size_t)i1 + 1] - ex[(size_t)i0]) * std::exp(-2.0 * ill_a * ly * ly);
     count += c;
   }
   return total / (double)count;
