@@ -192,38 +192,50 @@ __device__ void setup_part(const JobDev& jb, int lb, int nb) {
 // ------------------------------------------------- factor tables ---
 
 // Factor tables from FP64 phases (zero outside the grid and beyond N):
-//   Fc  back-propagation B operand: part of F_n(col), col 16 cb + l%16,
-//       spot n = 2 s + g/2 of K-step s;
-//   Ga  G_n(row) for row 16 rb + l%16, spot 2 s + g/2 (forms the A operand);
-//   Fn  forward B operand: part of F_n(col), spot 16 sb + l%16, column
-//       2 cp + g/2 of column pair cp;
+//   Fc  B operand of the final hologram: part of F_n(col), col 16 cb + l%16,
+//       spot n = 2 s + g/2 of K-step s (FP32);
+//   Ga  G_n(row) for row 16 rb + l%16 and spot n (forms the A operands);
+// and, for the iteration pass,
+//   Fs  back-propagation B operand, col 16 cb + l%16, spots 16 s + 4 g + q,
+//       and Fn  forward B operand, spot 16 sb + l%16, columns 16 cb + 4 g + q:
+//       half pairs (re, im) of the two parts of 2^kSplitBits F;
 //   Gv  G_n(row) for spot 16 sb + l%16 and rows 16 rb + 4 g + r (V sums).
 __device__ void sep_tables_part(const JobDev& jb, int lb, int nb) {
   const int W = jb.W, H = jb.H, N = jb.N;
   const int S16 = jb.mx_steps, Np = 16 * S16, KS = Np / 2;
-  const int CB = jb.mx_cblocks, RB = jb.mx_rblocks, CP = 8 * CB;
+  const int CB = jb.mx_cblocks, RB = jb.mx_rblocks;
+  const bool iter = jb.iter_tables != 0;
   const int64_t nF = (int64_t)(16 * CB) * Np, total = nF + (int64_t)(16 * RB) * Np;
   const double lf = jb.lambda_mm * jb.focal_mm;
   const double lf2 = lf * jb.focal_mm;
   const double kxy = jb.pitch_mm / (2.0 * lf), kz = jb.pitch_mm * jb.pitch_mm / (4.0 * lf2);
+  uint32_t* Fs = reinterpret_cast<uint32_t*>(jb.sepFs);
+  uint32_t* Fn = reinterpret_cast<uint32_t*>(jb.sepFn);
   for (int64_t k = (int64_t)lb * kSetupThreads + threadIdx.x; k < total; k += (int64_t)nb * kSetupThreads) {
     if (k < nF) {
       const int col = (int)(k / Np), n = (int)(k % Np);
-      float fr = 0.f, fi = 0.f;
+      double s = 0.0, c = 0.0;
       if (col < W && n < N) {
         const double L = (double)(2 * col - (W - 1));
         double t = jb.in.x[n] * kxy * L + jb.in.z[n] * kz * L * L;
         t -= rint(t);
-        double s, c;
         sincospi(2.0 * t, &s, &c);
-        fr = (float)c;
-        fi = (float)s;
       }
-      const int lgc = (n & 1) << 1, lgn = (col & 1) << 1;
-      for (int p = 0; p < 2; ++p) {
-        const float v = p ? fi : fr;
-        jb.sepFc[op_index4(col >> 4, n >> 1, KS, (col & 15) + 16 * (lgc + p))] = v;
-        jb.sepFn[op_index4(n >> 4, col >> 1, CP, (n & 15) + 16 * (lgn + p))] = v;
+      const int lgc = (n & 1) << 1;
+      jb.sepFc[op_index4(col >> 4, n >> 1, KS, (col & 15) + 16 * lgc)] = (float)c;
+      jb.sepFc[op_index4(col >> 4, n >> 1, KS, (col & 15) + 16 * (lgc + 1))] = (float)s;
+      if (iter) {
+        const double x = c * kSplitScale, y = s * kSplitScale;
+        float h[2];
+        const uint32_t hi = pack_halves((float)x, (float)y, h);
+        const uint32_t lo = h2_bits((float)(x - (double)h[0]), (float)(y - (double)h[1]));
+        const int cb = col >> 4, cl = col & 15, sb = n >> 4, nl = n & 15;
+        uint32_t* fs = Fs + 8 * fc_index(cb, sb, S16, cl + 16 * (nl >> 2)) + (nl & 3);
+        uint32_t* fn = Fn + 8 * fn_index(sb, cb, CB, nl + 16 * (cl >> 2)) + (cl & 3);
+        fs[0] = hi;
+        fs[4] = lo;
+        fn[0] = hi;
+        fn[4] = lo;
       }
     } else {
       const int64_t kk = k - nF;
@@ -237,11 +249,11 @@ __device__ void sep_tables_part(const JobDev& jb, int lb, int nb) {
         sincospi(2.0 * t, &s, &c);
         g = make_float2((float)c, (float)s);
       }
-      const int lga = (n & 1) << 1;
-      for (int p = 0; p < 2; ++p)
-        jb.sepGa[op_index4(row >> 4, n >> 1, KS, (row & 15) + 16 * (lga + p))] = g;
-      float2* Gv = reinterpret_cast<float2*>(jb.sepGv);
-      Gv[op_index(row >> 4, n >> 4, S16, (n & 15) + 16 * ((row & 15) >> 2)) * 4 + (row & 3)] = g;
+      jb.sepGa[ga_index4(row >> 4, n >> 1, KS, (row & 15) + 16 * (n & 1))] = g;
+      if (iter) {
+        float2* Gv = reinterpret_cast<float2*>(jb.sepGv);
+        Gv[op_index(row >> 4, n >> 4, S16, (n & 15) + 16 * ((row & 15) >> 2)) * 4 + (row & 3)] = g;
+      }
     }
   }
 }

@@ -190,9 +190,12 @@ struct JobDev {
   int32_t mx_cblocks;  // Wp / 16 with Wp = W rounded up to 64
   int32_t mx_rblocks;  // Hp / 16
   // FP32 separable passes (FP32 jobs)
-  float* sepFc;        // [Wp/16][Np/2][64]   back-propagation B operand
-  float* sepFn;        // [Np/16][Wp/2][64]   forward B operand
-  float2* sepGa;       // [Hp/16][Np/2][64]   G by row, per lane
+  float* sepFc;        // [Wp/16][Np/2][64]   B operand of the final hologram
+  float2* sepGa;       // [Hp/16][Np/2][32]   G by row and spot parity
+  // of the iteration pass (iter_tables), split into two FP16 parts each
+  int32_t iter_tables; // 0: no full-grid iteration (RS): these are not built
+  uint4* sepFs;        // [Wp/16][Np/16][64] x 2  back-propagation B operand
+  uint4* sepFn;        // [Np/16][Wp/16][64] x 2  forward B operand
   float4* sepGv;       // [Hp/16][Np/16][64] x 2 float4: G for the V sums
   // mixed-precision matrix-core passes: FP16 / FP32 tables
   uint4* mxFc;         // [Wp/16][Np/16][64] x 4 half2   (back-propagation operand)
@@ -344,6 +347,7 @@ hipError_t launch_pass_chain(const JobDev* jobs, const PassDesc* descs, int npas
 // full-grid forward sum is V_n = (1/M) sum_j conj(G_n(j)) sum_i u(j,i) conj(F_n(i)).
 constexpr int kSepTileH = 64;  // output tile of the separable passes: rows (16 per wave)
 constexpr int kSepTileW = 32;  // and columns
+constexpr int kSepRed = 128;   // spots whose sums a tile's waves bring together at a time
 struct SepDesc {
   int32_t block_begin;
   int32_t job;
@@ -373,10 +377,20 @@ struct SepDesc {
 
 PassPlan plan_sep(int W, int H);
 // Fused full-grid pass (back-propagation S = B F and forward T = U conj(F)^T
-// on the FP32 matrix cores, exact sums, update) or, with final != 0, the
-// full-grid hologram Phi = arg(B F).  max_steps: largest Np / 16.
+// on the matrix cores, exact sums, update) or, with final != 0, the
+// full-grid hologram Phi = arg(B F).  max_steps: largest Np / 16.  With one
+// descriptor, `head` holds what the start of its pass reads.
+struct SepHead {
+  const SpotRec* st = nullptr;              // state before the previous pass's update
+  const unsigned long long* tot = nullptr;  // the previous pass's total set (null: no update)
+  const float2* ga = nullptr;
+  const float* fc = nullptr;
+  const uint4* fs = nullptr;
+  int32_t N = 0, S16 = 0, W = 0, H = 0, tiles_x = 0, tiles_y = 0;
+  int32_t job = 0;                          // index of the job in the launch's table
+};
 void launch_sep_pass(const JobDev* jobs, const SepDesc* descs, int ndesc, int total_blocks,
-                     bool final, int max_steps, hipStream_t s);
+                     bool final, int max_steps, const SepHead& head, hipStream_t s);
 
 // ---- mixed-precision passes (FP16 matrix cores, FP32 sums) ----
 // A pass is the separable recast above on the matrix cores: per output tile

@@ -23,6 +23,19 @@ __device__ __forceinline__ int64_t op_index4(int blk, int step, int steps, int l
   return (((int64_t)blk * (steps >> 2) + (step >> 2)) * 64 + lane) * 4 + (step & 3);
 }
 
+// G by row for the same K-steps: the two lane groups of a spot (its real and
+// its imaginary part) read the same entry, so a step holds 32 of them, row
+// l % 16 and spot parity n % 2: lane32 = l % 16 + 16 (n % 2).
+__device__ __forceinline__ int64_t ga_index4(int blk, int step, int steps, int lane32) {
+  return (((int64_t)blk * (steps >> 2) + (step >> 2)) * 32 + lane32) * 4 + (step & 3);
+}
+
+// Split FP16 operands of the iteration pass: F times 2^kSplitBits as a sum of
+// two halves.  Tables in the layout of the mixed-precision operands below,
+// with two 16-byte words per lane (the hi pairs, then the lo pairs).
+constexpr int kSplitBits = 11;
+constexpr float kSplitScale = 2048.0f;
+
 // Mixed-precision passes, v_mfma_f32_16x16x32_f16 (lane l, e < 8, r < 4):
 //   A[l % 16][8 (l / 16) + e],  B[8 (l / 16) + e][l % 16],  D[4 (l / 16) + r][l % 16].
 // With K = 2 Np interleaved (k = 2 n + part), lane l of K-step s covers

@@ -114,6 +114,16 @@ __device__ __forceinline__ float swap_add(float x, bool rows) {
                       : __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
 }
+// Sums of a and of b over the four rows of 16 lanes: a's in the first row,
+// b's in the second.
+__device__ __forceinline__ float row_pair_sum(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a),
+                                                  __builtin_bit_cast(unsigned, b), false, false);
+  // rows (a0 + a1, b0 + b1, a2 + a3, b2 + b3), then the halves
+  return swap_add(__builtin_bit_cast(float, (unsigned)r[0]) +
+                      __builtin_bit_cast(float, (unsigned)r[1]),
+                  false);
+}
 template <int N>
 __device__ __forceinline__ float ror_add(float x) {
   return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(

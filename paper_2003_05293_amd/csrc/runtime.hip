@@ -450,6 +450,8 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
   j.mixed = s.precision == HG_PREC_MIXED ? 1 : 0;
   j.shared_e = (!j.mixed && tp.pass_form == 1 && pass_e_width(s.N) > 0) ? 1 : 0;
   L.separable = !j.mixed && tp.separable_full && !s.full_direct;
+  // (the single-pass entry points run an iteration without asking for one)
+  j.iter_tables = (L.separable && (s.iterations > 0 || s.hook)) ? 1 : 0;
   // compressed passes without an update of their own, where every pass up to
   // the final hologram takes deferred updates (a chained launch hands its
   // updates over inside the launch instead; a grid of one column has no
@@ -536,9 +538,12 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
   if (L.separable) {
     const size_t ops = (size_t)j.mx_steps * 64;  // operand lanes per 16-row/column block
     L.off_sepFc = take(sizeof(float) * 8 * ops * j.mx_cblocks);
-    L.off_sepFn = take(sizeof(float) * 8 * ops * j.mx_cblocks);
-    L.off_sepGa = take(sizeof(float2) * 8 * ops * j.mx_rblocks);
-    L.off_sepGv = take(sizeof(float2) * 4 * ops * j.mx_rblocks);
+    L.off_sepGa = take(sizeof(float2) * 4 * ops * j.mx_rblocks);
+    if (j.iter_tables) {
+      L.off_sepFs = take(sizeof(uint4) * 2 * ops * j.mx_cblocks);
+      L.off_sepFn = take(sizeof(uint4) * 2 * ops * j.mx_cblocks);
+      L.off_sepGv = take(sizeof(float2) * 4 * ops * j.mx_rblocks);
+    }
   }
   L.bytes = align_up(bytes, 256);
   return L;
@@ -577,9 +582,12 @@ JobDev bind_job(const JobLayout& L, const JobSpec& s, char* base, const double* 
   j.V = reinterpret_cast<double2*>(base + L.off_V);
   if (L.separable) {
     j.sepFc = reinterpret_cast<float*>(base + L.off_sepFc);
-    j.sepFn = reinterpret_cast<float*>(base + L.off_sepFn);
     j.sepGa = reinterpret_cast<float2*>(base + L.off_sepGa);
-    j.sepGv = reinterpret_cast<float4*>(base + L.off_sepGv);
+    if (j.iter_tables) {
+      j.sepFs = reinterpret_cast<uint4*>(base + L.off_sepFs);
+      j.sepFn = reinterpret_cast<uint4*>(base + L.off_sepFn);
+      j.sepGv = reinterpret_cast<float4*>(base + L.off_sepGv);
+    }
   }
   if (j.mixed) {
     j.mxFc = reinterpret_cast<uint4*>(base + L.off_mxFc);
@@ -717,6 +725,22 @@ void LaunchSet::add_forward_mx(const JobDev& j, const JobLayout& L, int index) {
 }
 
 namespace {
+SepHead sep_head(const JobDev& j, const SepDesc& d) {
+  SepHead h;
+  h.st = d.st_in;
+  h.tot = d.pending ? j.acc + (int64_t)d.prev_row * kAccReplicas * j.N * kAccSpotWords : nullptr;
+  h.ga = j.sepGa;
+  h.fc = j.sepFc;
+  h.fs = j.sepFs;
+  h.N = j.N;
+  h.S16 = j.mx_steps;
+  h.W = j.W;
+  h.H = j.H;
+  h.tiles_x = d.tiles_x;
+  h.tiles_y = d.tiles_y;
+  h.job = d.job;
+  return h;
+}
 PassHead pass_head(const JobDev& j, const PassDesc& d) {
   PassHead h;
   h.st = d.pending ? d.st_in : j.sp;
@@ -769,6 +793,7 @@ void LaunchSet::add_iteration(const JobDev& j, const JobLayout& L, int it, int i
     d.update = 1;
     d.V = j.V + (j.trace ? (size_t)(it - 1) * j.N : 0);
     plan_deferral(d, j, L, it);
+    if (sep.empty()) sep_start = sep_head(j, d);
     sep.push_back(d);
     sep_blocks += d.plan.blocks;
     sep_steps = std::max(sep_steps, j.mx_steps);
@@ -803,6 +828,7 @@ void LaunchSet::add_final(const JobDev& j, const JobLayout& L, int index) {
     SepDesc d = sep_desc(j, L, index, sep_blocks);
     d.out = j.phi;
     plan_deferral(d, j, L, j.iterations + 1);
+    if (sep.empty()) sep_start = sep_head(j, d);
     sep.push_back(d);
     sep_blocks += d.plan.blocks;
     sep_steps = std::max(sep_steps, j.mx_steps);
@@ -824,6 +850,12 @@ size_t LaunchSet::bytes() const {
          align_up(sizeof(SepDesc) * sep.size(), 256) +
          align_up(sizeof(BackDesc) * back.size(), 256) + align_up(sizeof(MxDesc) * mx.size(), 256) +
          align_up(sizeof(PassDesc) * mxp.size(), 256) + align_up(sizeof(PassDesc) * mxw.size(), 256);
+}
+
+void LaunchSet::clear_sep_deferral() {
+  for (SepDesc& d : sep) clear_deferral(d);
+  sep_start.st = nullptr;
+  sep_start.tot = nullptr;
 }
 
 // A launch of more deferring blocks than kSpreadBlocks gives each block
@@ -895,7 +927,7 @@ void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
   };
   if (!sep.empty())
     run(sep_final ? "k_sep_final" : "k_sep_pass", [&] {
-      launch_sep_pass(jobs, d_sep, (int)sep.size(), sep_blocks, sep_final, sep_steps, s);
+      launch_sep_pass(jobs, d_sep, (int)sep.size(), sep_blocks, sep_final, sep_steps, sep_start, s);
     });
   if (!dfr.empty())
     run("k_pass_subset", [&] {
@@ -1013,8 +1045,8 @@ hg_status Batch::build(const JobSpec* specs, int count, const TuneParams& tune,
     // compressed pass of the one-launch-per-pass form that stands in when
     // the cooperative launch is refused
     if ((size_t)passes < rounds_.size())
-      for (SepDesc& d : rounds_[passes].sep) clear_deferral(d);
-    for (SepDesc& d : final_.sep) clear_deferral(d);
+      rounds_[passes].clear_sep_deferral();
+    final_.clear_sep_deferral();
     for (PassDesc& d : rounds_[passes - 1].pass) {
       d.defer = 0;
       d.st_out = nullptr;

@@ -162,7 +162,7 @@ struct JobLayout {
   bool separable = false;
   size_t off_raw = 0, off_sp = 0, off_sp_alt = 0, off_coef = 0, off_tab = 0, off_perm = 0, off_partial = 0,
          off_gpart = 0, off_acc = 0, off_counters = 0, off_V = 0, off_sepFc = 0, off_sepFn = 0,
-         off_sepGa = 0, off_sepGv = 0, off_mxFc = 0, off_mxFn = 0, off_mxGa = 0, off_mxGv = 0,
+         off_sepFs = 0, off_sepGa = 0, off_sepGv = 0, off_mxFc = 0, off_mxFn = 0, off_mxGa = 0, off_mxGv = 0,
          off_rows = 0;
   size_t bytes = 0;
   bool raw_inline = false;  // the job's own scratch holds a copy of its spot arrays
@@ -198,6 +198,7 @@ struct LaunchSet {
   std::vector<PassDesc> wide;
   int wide_blocks = 0, wide_units = 1;
   std::vector<SepDesc> sep;
+  SepHead sep_start;  // of the first of them
   int sep_blocks = 0, sep_steps = 0;
   bool sep_final = false;
   std::vector<BackDesc> back;
@@ -239,6 +240,8 @@ struct LaunchSet {
   size_t stage(char* host, char* dev);
   // Several tiles per block where the launch has many blocks (stage() does it).
   void spread_tiles();
+  // Makes the set's separable passes update in their own tails.
+  void clear_sep_deferral();
   // Launches the set's kernels.  `capture`: no timing.
   void launch(const JobDev* jobs, hipStream_t s, bool capture) const;
 };
