@@ -304,7 +304,8 @@ void launch_pass_batch(const JobDev* jobs, const PassDesc* descs, int ndesc, int
                        int max_units, int e_width, hipStream_t s);
 // Compressed passes of `deferring` jobs: N <= kDeferMaxSpots (FP32) or
 // kBlock (mixed: FP16 back-propagation products accumulated in FP32).  With
-// one descriptor, `head` holds what the start of its pass reads.
+// one descriptor, `head` holds what the start of its pass reads.  large: the
+// launch fills the chip several times over (any value gives the same bits).
 constexpr int kDeferMaxSpots = 512;
 struct PassHead {
   const SpotRec* st = nullptr;              // state before the previous pass's update
@@ -315,7 +316,8 @@ struct PassHead {
   int32_t job = 0;                          // index of the job in the launch's table
 };
 void launch_pass_defer(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,
-                       int max_spots, bool mixed, const PassHead& head, hipStream_t s);
+                       int max_spots, bool mixed, bool large, const PassHead& head,
+                       hipStream_t s);
 // Compressed passes of the other mixed-precision jobs (more than one spot
 // unit per wave); descs and units as for launch_pass_batch.
 void launch_pass_mx(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,

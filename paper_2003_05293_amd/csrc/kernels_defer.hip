@@ -53,6 +53,74 @@ __device__ __forceinline__ PixCoord coord_of(const PassStart& h, int32_t p) {
   return pixel_coord(p, h.W, h.H, h.div_m, h.div_sh);
 }
 
+// Phase 2 of 33 ... 256 spots by chains.  A unit of the per-pixel pass sums
+// its slice's pixels in two chains, the even and the odd ones (its 64 lanes are
+// 64 spots, so the last chunk of N spots leaves lanes idle: 28 of 128 at N =
+// 100, a whole wave's work at N = 150).  Here the lanes of a wave are the 2^lgG
+// chains of all slices times 64 >> lgG spots: the same chains of the same
+// pixels in the same order, in ceil(N / (64 >> lgG)) <= 8 rounds, of which a wave
+// takes one or two (two share the reads of the pixels).  For launches that
+// fill the chip several times over, where the vector issue bounds the pass: 64
+// mixed holograms of 8 to 200 spots 12.89 to 12.08 ms, 32 of 100 spots 5.75 to
+// 5.65 ms.  One hologram's pass ends with its slowest wave, whose share of the
+// pixels does not get smaller, and the form's 70 VGPRs hold seven blocks per
+// compute unit instead of eight (1920 x 1152, N = 52: 265 to 279 us): there
+// the units stay.
+struct ChainMap {
+  int lgL;     // lanes (spots) per chain 2^lgL = 8, 16 or 32: also its pixels
+  int lgS;     // slices 2^lgS (two chains each)
+  int rounds;  // ceil(N / 2^lgL)
+  int stride;  // spots per chain in the table of sums
+};
+__device__ __forceinline__ ChainMap chain_map(int N) {
+  ChainMap m;
+  m.lgL = N <= 64 ? 3 : N <= 128 ? 4 : 5;
+  m.lgS = 5 - m.lgL;
+  m.rounds = (N + (1 << m.lgL) - 1) >> m.lgL;
+  m.stride = 8 << m.lgL;
+  return m;
+}
+template <int K>
+__device__ __forceinline__ void chain_rounds(int N, const ChainMap& m, int round, int lane,
+                                             const SpotRec* recs, const float4* px,
+                                             const float* pui, float2* red) {
+  const int L = 1 << m.lgL, c = lane >> m.lgL, g = lane & (L - 1);
+  // chain c: pixels of slice c / 2 (2 L of them) of parity c % 2
+  const int p0 = ((c >> 1) << (m.lgL + 1)) + (c & 1);
+  float cx[K], cy[K], cz[K], vr[K], vi[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int n = ((round + k * kWaves) << m.lgL) + g;
+    cx[k] = cy[k] = cz[k] = vr[k] = vi[k] = 0.f;
+    if (n < N) {
+      cx[k] = recs[n].cx;
+      cy[k] = recs[n].cy;
+      cz[k] = recs[n].cz;
+    }
+  }
+  const float4* q = px + p0;
+  const float* w = pui + p0;
+  for (int i = 0; i < L; i += 2, q += 4, w += 4) {
+    const float4 a0 = q[0], a1 = q[2];
+    const float b0 = w[0], b1 = w[2];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      forward_term(cx[k], cy[k], cz[k], a0, b0, vr[k], vi[k]);
+      forward_term(cx[k], cy[k], cz[k], a1, b1, vr[k], vi[k]);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    red[c * m.stride + ((round + k * kWaves) << m.lgL) + g] = make_float2(vr[k], vi[k]);
+}
+__device__ __forceinline__ void forward_chains(int N, const ChainMap& m, int role, int lane,
+                                               const SpotRec* recs, const float4* px,
+                                               const float* pui, float2* red) {
+  static_assert(kWaves == 4, "at most two of eight rounds per wave");
+  if (role + kWaves < m.rounds) chain_rounds<2>(N, m, role, lane, recs, px, pui, red);
+  else chain_rounds<1>(N, m, role, lane, recs, px, pui, red);  // (five rounds at least)
+}
+
 // One pass of one job.  MAXU: spot units per wave (1: N <= 256, 2: N <= 512).
 //
 // A block takes its tiles of 64 pixels in turn.  Per 64 pixels:
@@ -65,35 +133,37 @@ __device__ __forceinline__ PixCoord coord_of(const PassStart& h, int32_t p) {
 //  phase 2  lanes = spots over the wave's pixels, as in the per-pixel pass.
 // Then each component of the tile's sums is formed by one thread and added to
 // the pass's total set, re and im in neighbouring lanes.
-template <int MAXU, bool MX>
+template <int MAXU, bool MX, bool CHAINS>
 __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& plan, int lb,
                                             int tot_row, unsigned long long* acc, float ill_a,
                                             const SpotRec* recs, PixCoord c) {
   __shared__ float2 sw[2][kWaves][kTile];
   __shared__ float4 px[kWaves][kTile];
   __shared__ float pui[kWaves][kTile];
-  __shared__ float2 red[kWaves * MAXU][64];
+  // sums of the units (64 lanes each), or of the chains (cl.stride spots each)
+  __shared__ float2 red[kWaves * (CHAINS ? 2 : MAXU) * 64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int N = h.N;
   const LaneMap lm = lane_map(N);
   const int Lg = 1 << lm.lgL, R = 64 >> lm.lgL, S = 1 << lm.lgS;
   const int g = lane & (Lg - 1), r = lane >> lm.lgL;
-  float cx[MAXU], cy[MAXU], cz[MAXU];
-#pragma unroll
-  for (int k = 0; k < MAXU; ++k) {
-    const int u = wave + k * kWaves;
+  auto unit_rec = [&](int u) {  // cx, cy, cz of this lane's spot in unit u
     const int n = ((u >> lm.lgS) << lm.lgL) + g;
-    cx[k] = cy[k] = cz[k] = 0.f;
-    if (u < lm.U && n < N) {
-      cx[k] = recs[n].cx;
-      cy[k] = recs[n].cy;
-      cz[k] = recs[n].cz;
-    }
-  }
+    if (u >= lm.U || n >= N) return make_float3(0.f, 0.f, 0.f);
+    return make_float3(recs[n].cx, recs[n].cy, recs[n].cz);
+  };
+  float3 rec[MAXU];
+#pragma unroll
+  for (int k = 0; k < MAXU; ++k)
+    if (!CHAINS) rec[k] = unit_rec(wave + k * kWaves);
   const int n_lo = (int)((unsigned)(wave * N) / kWaves);
   const int n_hi = (int)((unsigned)((wave + 1) * N) / kWaves);
   const double scale = ldexp(1.0, plan.shift);
+  // (parts of one tile add up between the chains: those stay with the units)
+  const bool chains = CHAINS && N > 32 && plan.sub == 1;
+  const ChainMap cl = chain_map(N);
+  int turn = lb >> 8;  // which waves take the odd rounds: in turn over tiles and blocks
   // this thread's components of the tiles' sums (x = threadIdx.x + i kBlock)
   constexpr int kSums = 2 * MAXU;  // 2 N <= kSums kBlock
   unsigned long long sums[kSums];
@@ -141,24 +211,33 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
       }
       // (the wave's own rows: its LDS accesses complete in order)
       __builtin_amdgcn_wave_barrier();
+      if (chains) {
+        const int role = (wave + turn) & (kWaves - 1);
+        forward_chains(h.N, cl, role, lane, recs, px[wave], pui[wave], red);
+      } else {
 #pragma unroll
-      for (int k = 0; k < MAXU; ++k) {
-        const int u = wave + k * kWaves;
-        if (u >= lm.U) continue;
-        // (the order of the sums goes by the job's own unit count, also where
-        // it shares the launch with jobs of more spots)
-        if (MAXU == 1 || lm.U <= kWaves)
-          forward_unit<true>(lm, u, r, cx[k], cy[k], cz[k], px[wave], pui[wave], vr[k], vi[k]);
-        else
-          forward_unit<false>(lm, u, r, cx[k], cy[k], cz[k], px[wave], pui[wave], vr[k], vi[k]);
+        for (int k = 0; k < MAXU; ++k) {
+          const int u = wave + k * kWaves;
+          if (u >= lm.U) continue;
+          const float3 q = CHAINS ? unit_rec(u) : rec[k];
+          // (the order of the sums goes by the job's own unit count, also
+          // where it shares the launch with jobs of more spots)
+          if (MAXU == 1 || lm.U <= kWaves)
+            forward_unit<true>(lm, u, r, q.x, q.y, q.z, px[wave], pui[wave], vr[k], vi[k]);
+          else
+            forward_unit<false>(lm, u, r, q.x, q.y, q.z, px[wave], pui[wave], vr[k], vi[k]);
+        }
       }
       buf ^= 1;  // the next shares go to the other rows: one barrier is enough
     }
+    if (!chains) {
 #pragma unroll
-    for (int k = 0; k < MAXU; ++k) {
-      const int u = wave + k * kWaves;
-      if (u < lm.U) red[u][lane] = make_float2(vr[k], vi[k]);
+      for (int k = 0; k < MAXU; ++k) {
+        const int u = wave + k * kWaves;
+        if (u < lm.U) red[64 * u + lane] = make_float2(vr[k], vi[k]);
+      }
     }
+    turn += 1;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kSums; ++i) {
@@ -166,9 +245,13 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
       if (x >= 2 * N) break;
       const int n = x >> 1, part = x & 1;
       const int ch = n >> lm.lgL, gg = n & (Lg - 1);
-      const float* row = reinterpret_cast<const float*>(&red[ch << lm.lgS][gg]) + part;
+      const float* row = reinterpret_cast<const float*>(&red[64 * (ch << lm.lgS) + gg]) + part;
       float s = 0.f;
-      if (R == 1) {
+      if (chains) {  // the two chains of a slice, then the slices
+        const float* q = reinterpret_cast<const float*>(red) + x;
+        for (int sl = 0; sl < (1 << cl.lgS); ++sl)
+          s += q[2 * cl.stride * (2 * sl)] + q[2 * cl.stride * (2 * sl + 1)];
+      } else if (R == 1) {
         for (int sl = 0; sl < S; ++sl) s += row[2 * 64 * sl];
       } else {
         for (int sl = 0; sl < S; ++sl)
@@ -195,7 +278,7 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
 // of the row division from bit 16, parts per tile from bit 21; wh: W, H from
 // bit 15, bit 31 set with several passes (then only descs and jobs count and
 // `start` is the number of passes).
-template <int MAXU, bool MX>
+template <int MAXU, bool MX, bool CHAINS>
 __global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
     const SpotRec* st, const unsigned long long* tot, const int32_t* perm, int32_t start, int32_t P,
     int32_t count, uint32_t nss, uint32_t wh, uint32_t div_m, const PassDesc* __restrict__ descs,
@@ -243,25 +326,28 @@ __global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
     __syncthreads();
   }
   __builtin_amdgcn_s_setprio(0);
-  defer_tiles<MAXU, MX>(h, d.plan, lb, d.tot_row, jb.acc, jb.ill_a, recs, c);
+  defer_tiles<MAXU, MX, CHAINS>(h, d.plan, lb, d.tot_row, jb.acc, jb.ill_a, recs, c);
 }
 
 }  // namespace
 
 void launch_pass_defer(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,
-                       int max_spots, bool mixed, const PassHead& head, hipStream_t s) {
+                       int max_spots, bool mixed, bool large, const PassHead& head,
+                       hipStream_t s) {
   if (ndesc <= 0 || total_blocks <= 0) return;
   const dim3 grid(total_blocks), block(kBlock);
   const JobDev* j = ndesc == 1 ? jobs + head.job : jobs;
   const uint32_t nss = (uint32_t)head.N | ((uint32_t)head.row_div.sh << 16) | ((uint32_t)head.sub << 21);
   const uint32_t wh = (uint32_t)head.W | ((uint32_t)head.H << 15) | (ndesc > 1 ? 0x80000000u : 0u);
   const int32_t start = ndesc > 1 ? ndesc : head.start;
-#define HG_LAUNCH(U, M)                                                                          \
-  hipLaunchKernelGGL((k_pass_defer<U, M>), grid, block, 0, s, head.st, head.tot, head.perm,      \
+#define HG_LAUNCH(U, M, C)                                                                       \
+  hipLaunchKernelGGL((k_pass_defer<U, M, C>), grid, block, 0, s, head.st, head.tot, head.perm,   \
                      start, head.P, head.count, nss, wh, head.row_div.m, descs, j)
-  if (mixed) HG_LAUNCH(1, true);
-  else if (max_spots <= kBlock) HG_LAUNCH(1, false);
-  else HG_LAUNCH(2, false);
+  if (max_spots > kBlock) HG_LAUNCH(2, false, false);
+  else if (mixed && large) HG_LAUNCH(1, true, true);
+  else if (mixed) HG_LAUNCH(1, true, false);
+  else if (large) HG_LAUNCH(1, false, true);
+  else HG_LAUNCH(1, false, false);
 #undef HG_LAUNCH
 }
 

@@ -869,9 +869,10 @@ void LaunchSet::clear_sep_deferral() {
 // 3.24, 3.43, 3.58 ms.
 void LaunchSet::spread_tiles() {
   constexpr int kSpreadBlocks = 5120;
-  auto spread = [](std::vector<PassDesc>& list, int* total) {
+  auto spread = [](std::vector<PassDesc>& list, int* total, bool* large) {
     const int T = *total / kSpreadBlocks;
     if (T < 2) return;
+    *large = true;
     *total = 0;
     for (PassDesc& d : list) {
       d.block_begin = *total;
@@ -879,8 +880,8 @@ void LaunchSet::spread_tiles() {
       *total += d.plan.blocks;
     }
   };
-  spread(dfr, &dfr_blocks);
-  spread(mxp, &mxp_blocks);
+  spread(dfr, &dfr_blocks, &dfr_large);
+  spread(mxp, &mxp_blocks, &mxp_large);
 }
 
 size_t LaunchSet::stage(char* host, char* dev) {
@@ -931,7 +932,8 @@ void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
     });
   if (!dfr.empty())
     run("k_pass_subset", [&] {
-      launch_pass_defer(jobs, d_dfr, (int)dfr.size(), dfr_blocks, dfr_spots, false, dfr_head, s);
+      launch_pass_defer(jobs, d_dfr, (int)dfr.size(), dfr_blocks, dfr_spots, false, dfr_large,
+                        dfr_head, s);
     });
   if (!pass.empty())
     run(pass_name(pass, {}),
@@ -945,7 +947,8 @@ void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
         [&] { launch_backprop_batch(jobs, d_back, (int)back.size(), back_blocks, s); });
   if (!mxp.empty())
     run("k_mxp_subset", [&] {
-      launch_pass_defer(jobs, d_mxp, (int)mxp.size(), mxp_blocks, kBlock, true, mxp_head, s);
+      launch_pass_defer(jobs, d_mxp, (int)mxp.size(), mxp_blocks, kBlock, true, mxp_large, mxp_head,
+                        s);
     });
   if (!mxw.empty())
     run("k_mxp_subset",

@@ -191,6 +191,7 @@ struct LaunchSet {
   // mxp, mixed)
   std::vector<PassDesc> dfr;
   int dfr_blocks = 0, dfr_spots = 0;
+  bool dfr_large = false, mxp_large = false;  // several tiles per block
   PassHead dfr_head, mxp_head;  // of the first pass of each
   std::vector<PassDesc> pass;
   int pass_blocks = 0;

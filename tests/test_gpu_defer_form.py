@@ -65,3 +65,20 @@ def test_many_spots_equal_per_pixel_pass(N):
     assert np.array_equal(V[:I - 1], np.asarray(V_d)[:I - 1])
     phi_b, V_b = run(g, OPTICS, s, I, 0.4, 5, subset_block_cap=5)
     assert np.array_equal(phi, phi_b) and np.array_equal(V, V_b)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "mixed"])
+def test_large_launch_equals_alone(precision):
+    """A launch of several tiles per block (forward sums by chains from 33
+    spots on) against each hologram alone (by units)."""
+    import torch
+    g, I, c = Grid(641, 509), 3, 0.3
+    counts = [32, 33, 40, 64, 65, 100, 127, 128, 129, 150, 192, 200, 255, 256]
+    jobs = [hg.DeviceJob.from_spots(g, OPTICS, spot_cloud(n, n, g), I, c, n, precision=precision)
+            for n in counts]
+    print("[case] defer form, large launch", precision, flush=True)
+    hg.cswgs_batch(jobs)
+    torch.cuda.synchronize()
+    for n, job in zip(counts, jobs):
+        phi = hg.cswgs(g, OPTICS, spot_cloud(n, n, g), I, c, n, precision=precision)
+        assert np.array_equal(phi.cpu().numpy(), job.phi.cpu().numpy()), n
