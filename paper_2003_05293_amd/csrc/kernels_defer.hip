@@ -163,7 +163,7 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   // (parts of one tile add up between the chains: those stay with the units)
   const bool chains = CHAINS && N > 32 && plan.sub == 1;
   const ChainMap cl = chain_map(N);
-  int turn = lb >> 8;  // which waves take the odd rounds: in turn over tiles and blocks
+  int turn = 0;  // which waves take the odd rounds: in turn over the block's tiles
   // this thread's components of the tiles' sums (x = threadIdx.x + i kBlock)
   constexpr int kSums = 2 * MAXU;  // 2 N <= kSums kBlock
   unsigned long long sums[kSums];
@@ -308,15 +308,17 @@ __global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
   // the pixel of this lane in the block's first 64, requested with the state
   const int q0 = lb * h.sub * kTile + (int)(threadIdx.x & 63);
   const int32_t p0 = q0 < h.count ? window_pixel(h, q0) : 0;
-  // the updating waves: another pair of the four SIMDs for each of the blocks
-  // that share a compute unit (blocks 256 apart)
-  const int vt = (int)((threadIdx.x + 64u * (unsigned)((lb >> 8) & 3)) & (unsigned)(kBlock - 1));
+  // The same waves update in every block (and take the odd unit in every
+  // block): consecutive blocks of a compute unit start on another of its SIMDs,
+  // so the longer shares spread by themselves.  Moved on by one wave per block
+  // they meet on one SIMD again (1920 x 1152, N = 52: 255 to 266 us; N = 300,
+  // the units moved too: 942 to 1048 us).
   PixCoord c;
   if (h.tot) {
     PendingState<kMaxN> ps;
-    ps.load(h.st, h.tot, h.N, vt);
+    ps.load(h.st, h.tot, h.N);
     c = coord_of(h, p0);
-    ps.apply(jb, d, h.N, lb == 0, vt, recs, nullptr);
+    ps.apply(jb, d, h.N, lb == 0, recs, nullptr);
   } else {
     c = coord_of(h, p0);
     const HG_GLOBAL float* src = as_global(reinterpret_cast<const float*>(h.st));

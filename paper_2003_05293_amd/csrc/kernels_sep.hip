@@ -87,9 +87,9 @@ __device__ __forceinline__ void stage_coef(const SepStart& h, const SepDesc& d, 
                                            SpotRec* recs, float2* cs) {
   if (h.tot) {
     PendingState<kPendMaxSpots> ps;
-    ps.load(h.st, h.tot, h.N, threadIdx.x);
+    ps.load(h.st, h.tot, h.N);
     for (int n = h.N + threadIdx.x; n < 16 * h.S16; n += kBlock) cs[n] = make_float2(0.f, 0.f);
-    ps.apply(jb, d, h.N, h.lb == 0, threadIdx.x, recs, cs);
+    ps.apply(jb, d, h.N, h.lb == 0, recs, cs);
   } else {
     for (int n = threadIdx.x; n < 16 * h.S16; n += kBlock) {
       float2 c = make_float2(0.f, 0.f);

@@ -141,9 +141,9 @@ __device__ __forceinline__ float wave_tree_sum(float x) {
 // adds |V_n| for n = t, t + kBlock, ... in that order, starting from 0 (s
 // is that thread sum); the thread sums are added in a fixed tree within
 // each wave, then the wave sums in wave order.  Every thread must call it
-// (it holds a block barrier); t is the thread's index, or that of a
-// whole-wave rotation of the block.
-__device__ __forceinline__ float block_mean_of(float s, int N, int t) {
+// (it holds a block barrier).
+__device__ __forceinline__ float block_mean_of(float s, int N) {
+  const int t = threadIdx.x;
   __shared__ float wsum[kWaves];
   s = wave_tree_sum(s);
   if ((t & 63) == 0) wsum[t >> 6] = s;
@@ -212,7 +212,7 @@ __device__ void tail_final(const PassCtx& a, float2* vs) {
       a.counters[k * kCounterStride] = 0u;
   }
   if (!a.update) return;
-  const float mean = block_mean_of(msum, N, threadIdx.x);
+  const float mean = block_mean_of(msum, N);
   for (int n = threadIdx.x; n < N; n += kBlock) {
     const float2 v = vs[n];
     const float mag = mag32(v);
@@ -238,11 +238,7 @@ __device__ void tail_final(const PassCtx& a, float2* vs) {
 // C_n = A_n e^{i theta_n} in FP32 (LDS), formed as tail_final forms it.
 // Block 0 (lead) also clears the total set two passes back, stores the state
 // for the next pass when this pass defers in turn (the final state, in the
-// final hologram), the previous V when traced, and the status.  Threads of
-// index vt < kBlock take the spots vt, vt + kBlock, ... < N <= MAXN; vt is
-// the thread's index, or that of a whole-wave rotation of the block (the
-// waves of the blocks that share a compute unit then do this serial part on
-// different SIMDs).
+// final hologram), the previous V when traced, and the status. 
 //
 // load() only requests the values, so that what the caller does before
 // apply() overlaps their way.  The totals were completed by the launch before
@@ -259,11 +255,10 @@ struct PendingState {
   flt4_t lo[kPer], hi[kPer];
 
   // st: the state before the update; tot: the total set's first row.
-  __device__ __forceinline__ void load(const SpotRec* st, const unsigned long long* tot, int N,
-                                       int vt) {
+  __device__ __forceinline__ void load(const SpotRec* st, const unsigned long long* tot, int N) {
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const int n = vt + i * kBlock;
+      const int n = threadIdx.x + i * kBlock;
       sum[i] = ull2_t{0ull, 0ull};
       lo[i] = hi[i] = flt4_t{0.f, 0.f, 0.f, 0.f};
       if (n < N) {
@@ -282,7 +277,7 @@ struct PendingState {
 
   // D: PassDesc, SepDesc or MxDesc.  Every thread calls it (block barriers).
   template <typename D>
-  __device__ __forceinline__ void apply(const JobDev& jb, const D& d, int N, bool lead, int vt,
+  __device__ __forceinline__ void apply(const JobDev& jb, const D& d, int N, bool lead,
                                         SpotRec* recs, float2* cl) const {
     double2 t[kPer];
     float msum = 0.f;
@@ -290,12 +285,12 @@ struct PendingState {
     for (int i = 0; i < kPer; ++i) {
       t[i] = make_double2((double)(long long)sum[i][0] * d.prev_inv,
                           (double)(long long)sum[i][1] * d.prev_inv);
-      if (vt + i * kBlock < N) msum += mag32(field32(t[i]));
+      if ((int)threadIdx.x + i * kBlock < N) msum += mag32(field32(t[i]));
     }
-    const float mean = block_mean_of(msum, N, vt);
+    const float mean = block_mean_of(msum, N);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const int n = vt + i * kBlock;
+      const int n = threadIdx.x + i * kBlock;
       if (n >= N) continue;
       SpotRec r;
       r.cx = lo[i][0];
@@ -350,9 +345,8 @@ template <int MAXN, typename D>
 __device__ __forceinline__ void apply_pending(const JobDev& jb, const D& d, bool lead,
                                               SpotRec* recs, float2* cl) {
   PendingState<MAXN> ps;
-  ps.load(d.st_in, jb.acc + (int64_t)d.prev_row * kAccReplicas * jb.N * kAccSpotWords, jb.N,
-          threadIdx.x);
-  ps.apply(jb, d, jb.N, lead, threadIdx.x, recs, cl);
+  ps.load(d.st_in, jb.acc + (int64_t)d.prev_row * kAccReplicas * jb.N * kAccSpotWords, jb.N);
+  ps.apply(jb, d, jb.N, lead, recs, cl);
 }
 
 // Chained launch: the update of this pass is complete (this block's state
