@@ -619,8 +619,8 @@ __device__ void pass_block(const PassCtx& a, unsigned* grab, bool has_pre = fals
         }
       // a deferring pass adds into a row of its total set, others into
       // their tile's group
-      const int row = a.defer ? a.tot_row * kAccReplicas + tile % kAccReplicas
-                              : kAccGroupRow0 + tile / a.plan.group_size;
+      const int row = a.defer ? a.tot_row * acc_rows(N) + tile % acc_rows(N)
+                              : acc_group_row0(N) + tile / a.plan.group_size;
       acc_add(a.acc, N, a.plan.shift, row, n, acc);
     }
     if (threadIdx.x == 0) {
@@ -776,7 +776,7 @@ __device__ void pass_block_e(const PassCtx& a, unsigned* grab) {
     }
     // the tile's partials: spot n_lo + lane of each wave
     if (lane < cnt)
-      acc_add(a.acc, N, a.plan.shift, kAccGroupRow0 + tile / a.plan.group_size, n_lo + lane,
+      acc_add(a.acc, N, a.plan.shift, acc_group_row0(N) + tile / a.plan.group_size, n_lo + lane,
               rede[wave][lane]);
     if (threadIdx.x == 0) {
       done[ndone++] = tile;

@@ -52,20 +52,34 @@ struct PassPlan {
   int32_t shift;       // fixed-point scale 2^shift of the exact sums (|sum| <= pixels)
 };
 constexpr int32_t kMaxTiles = 8192;
-// Words per spot in the rows of exact sums: the atomic additions of
-// different spots go to different cache lines.
+// Words per spot in the rows of exact sums (re, im).
 constexpr int kAccSpotWords = 2;
-// Pass totals in the exact sums: kAccTotalRows sets of kAccReplicas rows.
+// Words per row: whole blocks of 64 bytes, so that no two rows share one.  Rows
+// that did made each other's additions wait: one pass of 2040 blocks at N =
+// 51 took 10.8 us, at N = 52 9.1 us.
+__host__ __device__ inline int acc_row_words(int N) { return ((N + 3) & ~3) * kAccSpotWords; }
+// Pass totals in the exact sums: kAccTotalRows sets of acc_rows(N) rows.
 // A compressed pass followed by another compressed pass of the same job
-// (a deferring pass) adds each tile's sums straight into row
-// tile mod kAccReplicas of set it mod 3 (it = iteration), with no counting:
-// the next pass reads the set after this launch has ended and adds its rows
+// (a deferring pass) adds its sums straight into one row of set it mod 3 (it =
+// iteration; which row goes by the block or the tile), with no counting: the
+// next pass reads the set after this launch has ended and adds its rows
 // (integer sums, so the total is the same whatever the split), and the pass
 // after that clears it.  Other passes hand their sums over through group
 // rows into the first row of their set (set 0 unless pending).
 constexpr int kAccTotalRows = 3;
-constexpr int kAccReplicas = 10;
-constexpr int kAccGroupRow0 = kAccTotalRows * kAccReplicas;  // row of group 0
+// Rows of a set.  Additions to one block of 64 bytes go one after another,
+// about 20 ns each, so few rows bound the passes of few spots (N = 52, 2040
+// blocks: 10.2 us with 8 rows, 9.1 with 10, 9.9 with 16).  Every block of the
+// next pass reads all of them, which counts from 257 spots on, two per thread
+// (N = 300: 38.7 us with 10 rows, 37.8 with 6).
+constexpr int kAccRows = 10, kAccRowsWide = 6;
+constexpr int kAccWideSpots = 257;
+__host__ __device__ inline int acc_rows(int N) {
+  return N < kAccWideSpots ? kAccRows : kAccRowsWide;
+}
+// Words per set, and the row of group 0.
+__host__ __device__ inline int acc_set_words(int N) { return acc_rows(N) * acc_row_words(N); }
+__host__ __device__ inline int acc_group_row0(int N) { return kAccTotalRows * acc_rows(N); }
 // Fixed-point scale of the exact sums of a pass over `pixels` pixels: every
 // term has magnitude <= 1, so |sum| * 2^shift <= 2^62.
 int sum_shift(int64_t pixels);
@@ -166,12 +180,12 @@ struct JobDev {
   float* phi;          // [H][W] output hologram (or input of a forward test pass)
   float2* partial;     // [max pass tiles][N] (mixed-precision passes)
   double2* gpart;      // [max pass groups][N] (mixed-precision passes)
-  // exact fixed-point sums of the FP32 passes: rows 0..kAccGroupRow0-1 the
-  // sets of pass totals, row kAccGroupRow0 + g group g; per spot a (re, im) two's-
+  // exact fixed-point sums of the FP32 passes: the sets of pass
+  // totals, then row acc_group_row0(N) + g for group g; per spot a (re, im) two's-
   // complement pair at the start of an entry of kAccSpotWords words; zero
   // between passes, except a total that a deferred update leaves for the
   // next pass
-  unsigned long long* acc;  // [kAccGroupRow0 + max pass groups][N][kAccSpotWords]
+  unsigned long long* acc;  // [acc_group_row0(N) + max pass groups][acc_row_words(N)]
   int64_t acc_len;
   unsigned* counters;  // [max pass groups + 1] group and pass counters, kCounterStride apart
   unsigned* grab;      // [iterations + 2] tile counters of the passes (PassDesc::grab_slot)

@@ -261,8 +261,8 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
     }
     if (tile + plan.blocks < plan.tiles) __syncthreads();  // red is rewritten
   }
-  unsigned long long* out =
-      acc + (int64_t)(tot_row * kAccReplicas + lb % kAccReplicas) * N * kAccSpotWords;
+  const int rows = MAXU == 1 ? kAccRows : acc_rows(N);
+  unsigned long long* out = acc + (tot_row * rows + lb % rows) * acc_row_words(N);
 #pragma unroll
   for (int i = 0; i < kSums; ++i) {
     const int x = threadIdx.x + i * kBlock;
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
     jp += dp->job;
     lb -= dp->block_begin;
     h = PassStart{dp->pending ? dp->st_in : jp->sp,
-                  dp->pending ? jp->acc + (int64_t)dp->prev_row * kAccReplicas * jp->N * kAccSpotWords
+                  dp->pending ? jp->acc + dp->prev_row * acc_set_words(jp->N)
                               : nullptr,
                   dp->ps.perm, (int)dp->ps.start, dp->ps.M, dp->ps.count, jp->N, dp->plan.sub,
                   jp->W, jp->H, jp->row_div.m, jp->row_div.sh};

@@ -170,8 +170,8 @@ __device__ void mx_tail(const JobDev& jb, const MxDesc& d, int lb, const SpotRec
   // the previous pass's total set, which every block has read, is cleared
   if (d.pending) {
     HG_GLOBAL unsigned long long* q =
-        as_global_mut(jb.acc + (int64_t)d.prev_row * kAccReplicas * N * kAccSpotWords);
-    for (int k = threadIdx.x; k < kAccReplicas * N * kAccSpotWords; k += kBlock)
+        as_global_mut(jb.acc + d.prev_row * acc_set_words(N));
+    for (int k = threadIdx.x; k < acc_set_words(N); k += kBlock)
       __hip_atomic_store(q + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (!d.update) return;
@@ -441,7 +441,7 @@ __global__ __launch_bounds__(kBlock, 3) void k_mx_pass(const JobDev* __restrict_
           v.y += red[w][threadIdx.x].y;
         }
         if (d.defer)
-          acc_add(jb.acc, N, d.plan.shift, d.tot_row * kAccReplicas + lb % kAccReplicas, n, v);
+          acc_add(jb.acc, N, d.plan.shift, d.tot_row * acc_rows(N) + lb % acc_rows(N), n, v);
         else
           store_dev(jb.partial + (int64_t)lb * N + n, v);
       }

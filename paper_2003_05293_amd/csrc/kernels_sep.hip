@@ -66,7 +66,7 @@ __device__ __forceinline__ SepStart sep_start(const SpotRec* st, const unsigned 
     h.tx = h.lb - h.ty * dp->tiles_x;
     h.st = dp->st_in;
     h.tot = dp->pending
-                ? jp->acc + (int64_t)dp->prev_row * kAccReplicas * jp->N * kAccSpotWords
+                ? jp->acc + dp->prev_row * acc_set_words(jp->N)
                 : nullptr;
     h.ga = jp->sepGa;
     h.f = FINAL ? (const void*)jp->sepFc : (const void*)jp->sepFs;
@@ -476,8 +476,8 @@ __global__ __launch_bounds__(kBlock, 3) void k_sep_iter(
   const int CB = jb.mx_cblocks;
   const int grp = h.lb / d.plan.group_size;
   const int row =
-      d.defer ? d.tot_row * kAccReplicas + h.lb % kAccReplicas : kAccGroupRow0 + grp;
-  unsigned long long* out = jb.acc + (int64_t)row * N * kAccSpotWords;
+      d.defer ? d.tot_row * acc_rows(N) + h.lb % acc_rows(N) : acc_group_row0(N) + grp;
+  unsigned long long* out = jb.acc + (int64_t)row * acc_row_words(N);
   // T carries kSplitScale twice (exact powers of two)
   const double unit = ldexp(1.0, d.plan.shift - 2 * kSplitBits);
   for (int b0 = 0; b0 < S16; b0 += kSepRed / 16) {

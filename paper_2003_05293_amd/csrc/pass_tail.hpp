@@ -69,13 +69,12 @@ __device__ __forceinline__ void load_recs_dev(const SpotRec* sp, int N, SpotRec*
 // fixed-point integer (scale 2^shift, |sum over the pass| <= pixels, so no
 // sum overflows) and added with device-scope integer atomics: integer
 // addition is associative, so the sums do not depend on the order in which
-// tiles, groups or blocks arrive.  Rows: the sets of pass totals (rows
-// 0..kAccGroupRow0-1, kAccReplicas per set), then row kAccGroupRow0 + g =
-// group g.
+// tiles, groups or blocks arrive.  Rows: the sets of pass totals (acc_rows(N)
+// each), then row acc_group_row0(N) + g = group g.
 __device__ __forceinline__ void acc_add(unsigned long long* acc, int N, int shift, int row, int n,
                                         float2 v) {
   const double scale = ldexp(1.0, shift);
-  unsigned long long* p = acc + ((int64_t)row * N + n) * kAccSpotWords;
+  unsigned long long* p = acc + row * acc_row_words(N) + n * kAccSpotWords;
   atomicAdd(p, (unsigned long long)llrint((double)v.x * scale));
   atomicAdd(p + 1, (unsigned long long)llrint((double)v.y * scale));
 }
@@ -92,8 +91,8 @@ __device__ __forceinline__ unsigned long long take_dev(unsigned long long* p) {
 __device__ bool tail_group(const PassCtx& a, int g, int* flag) {
   for (int k = threadIdx.x; k < 2 * a.N; k += kBlock) {
     const int64_t e = (int64_t)(k >> 1) * kAccSpotWords + (k & 1);  // spot k / 2, part k % 2
-    const unsigned long long v = take_dev(a.acc + (int64_t)(kAccGroupRow0 + g) * a.N * kAccSpotWords + e);
-    atomicAdd(a.acc + (int64_t)a.tot_row * kAccReplicas * a.N * kAccSpotWords + e, v);
+    const unsigned long long v = take_dev(a.acc + (acc_group_row0(a.N) + g) * acc_row_words(a.N) + e);
+    atomicAdd(a.acc + a.tot_row * acc_set_words(a.N) + e, v);
   }
   return arrive_last(&a.counters[a.plan.ngroups * kCounterStride], (unsigned)a.plan.ngroups, flag);
 }
@@ -183,7 +182,7 @@ __device__ __forceinline__ bool update_rec(SpotRec& r, float2 v, float mag, floa
 __device__ void tail_final(const PassCtx& a, float2* vs) {
   const int N = a.N;
   const double inv = ldexp(1.0, -a.plan.shift) * a.inv_count;
-  unsigned long long* tot = a.acc + (int64_t)a.tot_row * kAccReplicas * N * kAccSpotWords;
+  unsigned long long* tot = a.acc + a.tot_row * acc_set_words(N);
   float msum = 0.f;
   for (int n = threadIdx.x; n < N; n += kBlock) {
     const long long re = (long long)take_dev(tot + (int64_t)n * kAccSpotWords);
@@ -199,8 +198,8 @@ __device__ void tail_final(const PassCtx& a, float2* vs) {
   // before counting its tiles, is cleared
   if (a.pend_row >= 0) {
     HG_GLOBAL unsigned long long* q =
-        as_global_mut(a.acc + (int64_t)a.pend_row * kAccReplicas * N * kAccSpotWords);
-    for (int k = threadIdx.x; k < kAccReplicas * N * kAccSpotWords; k += kBlock)
+        as_global_mut(a.acc + a.pend_row * acc_set_words(N));
+    for (int k = threadIdx.x; k < acc_set_words(N); k += kBlock)
       __hip_atomic_store(q + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   // the counters are ready for the next pass (kernel end orders these
@@ -256,6 +255,13 @@ struct PendingState {
 
   // st: the state before the update; tot: the total set's first row.
   __device__ __forceinline__ void load(const SpotRec* st, const unsigned long long* tot, int N) {
+    if (MAXN < kAccWideSpots || N < kAccWideSpots) load_rows<kAccRows>(st, tot, N);
+    else load_rows<kAccRowsWide>(st, tot, N);
+  }
+  template <int ROWS>
+  __device__ __forceinline__ void load_rows(const SpotRec* st, const unsigned long long* tot,
+                                            int N) {
+    const int stride = acc_row_words(N) / kAccSpotWords;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const int n = threadIdx.x + i * kBlock;
@@ -263,14 +269,14 @@ struct PendingState {
       lo[i] = hi[i] = flt4_t{0.f, 0.f, 0.f, 0.f};
       if (n < N) {
         const HG_GLOBAL ull2_t* q = as_global(reinterpret_cast<const ull2_t*>(tot)) + n;
-        ull2_t v[kAccReplicas];
+        ull2_t v[ROWS];
 #pragma unroll
-        for (int r = 0; r < kAccReplicas; ++r) v[r] = q[(int64_t)r * N];
+        for (int r = 0; r < ROWS; ++r) v[r] = q[r * stride];
         const HG_GLOBAL flt4_t* s = as_global(reinterpret_cast<const flt4_t*>(st + n));
         lo[i] = s[0];
         hi[i] = s[1];
 #pragma unroll
-        for (int r = 0; r < kAccReplicas; ++r) sum[i] += v[r];
+        for (int r = 0; r < ROWS; ++r) sum[i] += v[r];
       }
     }
   }
@@ -335,8 +341,8 @@ struct PendingState {
     __syncthreads();
     if (lead && d.clear_row >= 0) {
       HG_GLOBAL unsigned long long* q =
-          as_global_mut(jb.acc + (int64_t)d.clear_row * kAccReplicas * N * kAccSpotWords);
-      for (int k = threadIdx.x; k < kAccReplicas * N * kAccSpotWords; k += kBlock)
+          as_global_mut(jb.acc + d.clear_row * acc_set_words(N));
+      for (int k = threadIdx.x; k < acc_set_words(N); k += kBlock)
         __hip_atomic_store(q + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
@@ -345,7 +351,7 @@ template <int MAXN, typename D>
 __device__ __forceinline__ void apply_pending(const JobDev& jb, const D& d, bool lead,
                                               SpotRec* recs, float2* cl) {
   PendingState<MAXN> ps;
-  ps.load(d.st_in, jb.acc + (int64_t)d.prev_row * kAccReplicas * jb.N * kAccSpotWords, jb.N);
+  ps.load(d.st_in, jb.acc + d.prev_row * acc_set_words(jb.N), jb.N);
   ps.apply(jb, d, jb.N, lead, recs, cl);
 }
 

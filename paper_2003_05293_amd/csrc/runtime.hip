@@ -529,7 +529,7 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
     L.off_gpart = take(sizeof(double2) * (size_t)max_groups * s.N);
   }
   if (!j.mixed || j.compressed) {  // exact fixed-point sums of the per-pixel passes
-    j.acc_len = (int64_t)(kAccGroupRow0 + acc_groups) * s.N * kAccSpotWords;
+    j.acc_len = (int64_t)(acc_group_row0(s.N) + acc_groups) * acc_row_words(s.N);
     L.off_acc = take(sizeof(unsigned long long) * (size_t)j.acc_len);
   }
   L.off_counters = take(sizeof(unsigned) * (size_t)j.counters_len);
@@ -728,7 +728,7 @@ namespace {
 SepHead sep_head(const JobDev& j, const SepDesc& d) {
   SepHead h;
   h.st = d.st_in;
-  h.tot = d.pending ? j.acc + (int64_t)d.prev_row * kAccReplicas * j.N * kAccSpotWords : nullptr;
+  h.tot = d.pending ? j.acc + d.prev_row * acc_set_words(j.N) : nullptr;
   h.ga = j.sepGa;
   h.fc = j.sepFc;
   h.fs = j.sepFs;
@@ -744,7 +744,7 @@ SepHead sep_head(const JobDev& j, const SepDesc& d) {
 PassHead pass_head(const JobDev& j, const PassDesc& d) {
   PassHead h;
   h.st = d.pending ? d.st_in : j.sp;
-  h.tot = d.pending ? j.acc + (int64_t)d.prev_row * kAccReplicas * j.N * kAccSpotWords : nullptr;
+  h.tot = d.pending ? j.acc + d.prev_row * acc_set_words(j.N) : nullptr;
   h.perm = d.ps.perm;
   h.start = (int32_t)d.ps.start;
   h.P = d.ps.M;
