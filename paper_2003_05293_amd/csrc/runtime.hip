@@ -858,30 +858,42 @@ void LaunchSet::clear_sep_deferral() {
   sep_start.tot = nullptr;
 }
 
-// A launch of more deferring blocks than kSpreadBlocks gives each block
-// several tiles (T for all passes of the launch): a block then forms the
-// updated state once for T tiles and adds their exact sums to the totals once,
-// and the next tile's pixel indices are on their way during a tile's
-// arithmetic.  Results do not depend on it.  The chip holds 2048 such blocks;
-// two and a half times as many keep its end even.  Measured with T = 1, 2, 4,
-// 8, 16: 32 holograms of 1152^2 (41,472 tiles a round) 7.06, 6.50, 6.30, 6.17,
-// 6.14 ms; a burst of 16 served holograms (about 27,000 tiles) 3.53, 3.27,
-// 3.24, 3.43, 3.58 ms.
+// A launch of many deferring blocks gives each block several tiles: a block
+// then forms the updated state once for all of them and adds their exact sums
+// to the totals once, and the next tile's pixel indices are on their way during
+// a tile's arithmetic.  Results do not depend on it.  The chip holds 2048 such
+// blocks (1280 of more than 256 spots).
+// - From 2 kSpreadBlocks blocks on, T tiles per block (the same T for all passes
+//   of the launch): two and a half times what the chip holds keeps the launch's
+//   end even.  Measured with T = 1, 2, 4, 8, 16: 32 holograms of 1152^2 (41,472
+//   tiles a round) 7.06, 6.50, 6.30, 6.17, 6.14 ms; a burst of 16 served
+//   holograms (about 27,000 tiles) 3.53, 3.27, 3.24, 3.43, 3.58 ms.
+// - One pass of up to 256 spots: no more blocks than the chip holds; the first
+//   take a tile more (N = 20, 2592 to 5184 tiles: 10.2 to 9.5 and 15.7 to 12.2
+//   us per pass; N = 100: 16.5 to 15.9 and 27.6 to 27.1 us).  Beyond 256 spots
+//   it gains nothing (N = 300, 2160 tiles: 920 to 926 us per hologram).
+// - Several passes: kFewBlocks at most.  With 2048 the blocks of two tiles are
+//   the first of every pass, not of the launch, and some end late (two passes
+//   of 1296 tiles, N = 200: 28.9 us as they are, 30.0 us; six, N = 100: 42.8 us,
+//   43.3 with 2048, 41.2 with 4096 blocks).
 void LaunchSet::spread_tiles() {
-  constexpr int kSpreadBlocks = 5120;
-  auto spread = [](std::vector<PassDesc>& list, int* total, bool* large) {
-    const int T = *total / kSpreadBlocks;
-    if (T < 2) return;
-    *large = true;
+  constexpr int kSpreadBlocks = 5120, kFewBlocks = 4096, kOneBlocks = 2048;
+  auto spread = [](std::vector<PassDesc>& list, int* total, int spots, bool* large) {
+    const int64_t all = *total, T = all / kSpreadBlocks;
+    *large = T >= 2;
+    const int64_t keep = *large ? (all + T - 1) / T : list.size() > 1 ? kFewBlocks
+                                 : spots > kBlock ? all : kOneBlocks;
+    if (keep >= all) return;
     *total = 0;
     for (PassDesc& d : list) {
       d.block_begin = *total;
-      d.plan.blocks = (d.plan.blocks + T - 1) / T;
+      d.plan.blocks = (int)(*large ? (d.plan.blocks + T - 1) / T
+                                   : (d.plan.blocks * keep + all - 1) / all);
       *total += d.plan.blocks;
     }
   };
-  spread(dfr, &dfr_blocks, &dfr_large);
-  spread(mxp, &mxp_blocks, &mxp_large);
+  spread(dfr, &dfr_blocks, dfr_spots, &dfr_large);
+  spread(mxp, &mxp_blocks, kBlock, &mxp_large);
 }
 
 size_t LaunchSet::stage(char* host, char* dev) {

@@ -82,3 +82,25 @@ def test_large_launch_equals_alone(precision):
     for n, job in zip(counts, jobs):
         phi = hg.cswgs(g, OPTICS, spot_cloud(n, n, g), I, c, n, precision=precision)
         assert np.array_equal(phi.cpu().numpy(), job.phi.cpu().numpy()), n
+
+
+@pytest.mark.parametrize("N", [20, 100])
+def test_more_tiles_than_resident_blocks(N):
+    """One pass of more than 2048 tiles (some blocks take two) against the
+    chained launch, and three passes of 6600 tiles together against each
+    alone."""
+    import torch
+    g, I, c = Grid(641, 509), 3, 0.43  # 140,292 window pixels
+    spots = [spot_cloud(N + k, N + k, g) for k in range(3)]
+    print("[case] defer form, more tiles than resident blocks", N, flush=True)
+    alone = []
+    for s in spots:
+        phi, V = run(g, OPTICS, s, I, c, 3)
+        phi_c, V_c = run(g, OPTICS, s, I, c, 3, chain_passes=1)
+        assert np.array_equal(phi, phi_c) and np.array_equal(V, V_c)
+        alone.append(phi)
+    jobs = [hg.DeviceJob.from_spots(g, OPTICS, s, I, c, 3) for s in spots]
+    hg.cswgs_batch(jobs)
+    torch.cuda.synchronize()
+    for phi, job in zip(alone, jobs):
+        assert np.array_equal(phi, job.phi.cpu().numpy())
