@@ -163,6 +163,18 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   // (parts of one tile add up between the chains: those stay with the units)
   const bool chains = CHAINS && N > 32 && plan.sub == 1;
   const ChainMap cl = chain_map(N);
+  // The oldest wave of a SIMD issues first, so the blocks of a compute unit
+  // finish one after another, and the last ones run alone, where a wave issues
+  // at half the rate.  Priorities that fall along the tile keep the blocks
+  // level instead: all of them up to 256 spots, the last four of a compute
+  // unit in mixed precision and beyond 256 spots (whose blocks do not all fit
+  // at once).  1152^2, N = 100: 369 to 349 us (pass 10.75 to 10.05 us), mixed
+  // 372 to 362 us; N = 200, 2040 tiles 22.0 to 21.2 us; N = 512 50.5 to 48.8 us.
+  // Up to 64 spots the additions at the blocks' ends bound the pass, and even
+  // ends crowd them (N = 52, 2040 tiles: 9.0 to 10.7 us): those stay as they
+  // are, as do launches of several tiles per block.
+  const bool paced = !CHAINS && N > 64;
+  const bool late = paced && ((MAXU == 1 && !MX) || lb + 4 * 256 >= plan.blocks);
   int turn = 0;  // which waves take the odd rounds: in turn over the block's tiles
   // this thread's components of the tiles' sums (x = threadIdx.x + i kBlock)
   constexpr int kSums = 2 * MAXU;  // 2 N <= kSums kBlock
@@ -178,6 +190,7 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
 #pragma unroll
     for (int k = 0; k < MAXU; ++k) vr[k] = vi[k] = 0.f;
     for (int st = 0; st < plan.sub; ++st) {
+      if (paced) __builtin_amdgcn_s_setprio(2);
       const int32_t q = (tile * plan.sub + st) * kTile + lane;
       const bool valid = q < h.count;
       if (tile != lb || st != 0) c = coord_of(h, next);
@@ -186,6 +199,7 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
       next = qn < h.count ? window_pixel(h, qn) : 0;
       sw[buf][wave][lane] =
           MX ? backprop_field_mx_lds(recs, n_lo, n_hi, c) : backprop_field_lds(recs, n_lo, n_hi, c);
+      if (late) __builtin_amdgcn_s_setprio(1);
       __syncthreads();
       {
         float4 rec = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -237,6 +251,7 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
         if (u < lm.U) red[64 * u + lane] = make_float2(vr[k], vi[k]);
       }
     }
+    if (paced) __builtin_amdgcn_s_setprio(0);
     turn += 1;
     __syncthreads();
 #pragma unroll
