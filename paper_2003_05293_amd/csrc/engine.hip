@@ -308,18 +308,17 @@ hg_status hg_engine_step(hg_engine* e, void* stream, int32_t* pending_out) {
   if (!pro.empty()) std::memcpy(st + o_pro, pro.data(), sizeof(hg::PrologueSlice) * pro.size());
   iter.stage(st + o_iter, e->step_buf.p + o_iter);
   fin.stage(st + o_fin, e->step_buf.p + o_fin);
-  HG_HIP(hipMemcpyAsync(e->step_buf.p, st, table_bytes, hipMemcpyHostToDevice, s));
+  std::vector<hg::Staging::Piece> pieces = {{e->step_buf.p, 0, table_bytes}};
   size_t so = table_bytes;
   for (int si : fresh) {
     Slot& sl = e->slots[si];
     if (sl.req.spec.spots_on_device) continue;
     const size_t nb = sizeof(double) * sl.req.spots.size();
     std::memcpy(st + so, sl.req.spots.data(), nb);
-    HG_HIP(hipMemcpyAsync(e->pool.p + sl.off + sl.layout.off_raw, st + so, nb,
-                          hipMemcpyHostToDevice, s));
+    pieces.push_back({e->pool.p + sl.off + sl.layout.off_raw, so, nb});
     so += nb;
   }
-  HG_TRY(e->staging.mark_copied(s));
+  HG_TRY(e->staging.copy(pieces, true, s));
   const hg::JobDev* slots_dev = reinterpret_cast<const hg::JobDev*>(e->step_buf.p + o_table);
   if (!newjobs.empty()) {
     const hg::JobDev* new_dev = reinterpret_cast<const hg::JobDev*>(e->step_buf.p + o_new);

@@ -295,6 +295,16 @@ struct PrologueSlice {
 };
 int prologue_setup_blocks(const JobDev& j);
 int prologue_table_blocks(const JobDev& j);  // 0 without matrix-core passes
+// Copies up to kUploadSegs pieces of pinned host memory to the device in one
+// launch (all of them multiples of 16 bytes, words = bytes / 16); done (or null) is recorded
+// as the launch's own completion.
+constexpr int kUploadSegs = 16;
+struct UploadSegs {
+  const unsigned long long* src[kUploadSegs];
+  ulonglong2* dst[kUploadSegs];
+  int32_t words[kUploadSegs];
+};
+void launch_upload(const UploadSegs& segs, int n, hipEvent_t done, hipStream_t s);
 void launch_prologue(const JobDev* jobs, const PrologueSlice* slices, int nslices,
                      int total_blocks, hipStream_t s);
 // Random pixel order of the compressed jobs; slices[] maps blocks to jobs.

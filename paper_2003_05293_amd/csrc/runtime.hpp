@@ -83,6 +83,13 @@ struct Staging {
   bool pending = false;
   bool adopted = false;
   hg_status acquire(size_t bytes);             // waits for the previous copy, grows
+  // Copies pieces of the area (offset, bytes) to the device; mark: records
+  // the event after them.
+  struct Piece {
+    void* dst;
+    size_t off, bytes;
+  };
+  hg_status copy(const std::vector<Piece>& pieces, bool mark, hipStream_t s);
   hg_status mark_copied(hipStream_t s);        // records the event after the copies
   void adopt(char* q, size_t n, hipEvent_t ev);
   void release();
