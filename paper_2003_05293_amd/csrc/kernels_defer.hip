@@ -170,11 +170,14 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   // unit in mixed precision and beyond 256 spots (whose blocks do not all fit
   // at once).  1152^2, N = 100: 369 to 349 us (pass 10.75 to 10.05 us), mixed
   // 372 to 362 us; N = 200, 2040 tiles 22.0 to 21.2 us; N = 512 50.5 to 48.8 us.
-  // Up to 64 spots the additions at the blocks' ends bound the pass, and even
-  // ends crowd them (N = 52, 2040 tiles: 9.0 to 10.7 us): those stay as they
-  // are, as do launches of several tiles per block.
-  const bool paced = !CHAINS && N > 64;
-  const bool late = paced && ((MAXU == 1 && !MX) || lb + 4 * 256 >= plan.blocks);
+  // In launches of several tiles per block the blocks' phases interleave the
+  // better for it: 32 such holograms 5.65 to 5.48 ms, 64 mixed ones 12.1 to 11.5
+  // ms.  Up to 64 spots the additions at the blocks' ends bound the pass, and
+  // even ends crowd them (N = 52, 2040 tiles: 9.0 to 10.7 us; ten holograms, two
+  // tiles per block, N = 16: 31.4 to 32.2 us a round): there only launches of many
+  // tiles per block gain (eight, N = 52: 111 to 106 us; five, served: none).
+  const bool paced = N > 64 || (CHAINS && plan.tiles >= 6 * plan.blocks);
+  const bool late = paced && (CHAINS || (MAXU == 1 && !MX) || lb + 4 * 256 >= plan.blocks);
   int turn = 0;  // which waves take the odd rounds: in turn over the block's tiles
   // this thread's components of the tiles' sums (x = threadIdx.x + i kBlock)
   constexpr int kSums = 2 * MAXU;  // 2 N <= kSums kBlock
