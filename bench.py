@@ -74,8 +74,8 @@ KERNELS = ("k_prologue", "k_perm", "k_sep_pass", "k_sep_final", "k_pass_subset",
 # summary committed under profiles/ (FETCH_SIZE and WRITE_SIZE, each scaled
 # by what the same counter reads for a copy of known size).  It holds only
 # while the kernel's sources are those the counters were taken on.
-TRAFFIC_SOURCES = ("kernels.hip", "kernels.hpp", "pass_tail.hpp", "device_common.hpp",
-                   "device_math.hpp")
+TRAFFIC_SOURCES = ("kernels_defer.hip", "kernels.hpp", "pass_tail.hpp", "pixel_pass.hpp",
+                   "device_common.hpp", "device_math.hpp")
 
 
 def kernel_sources_sha256() -> str:

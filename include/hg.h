@@ -235,9 +235,10 @@ hg_status hg_cswgs_ex(const hg_grid *grid, const hg_optics *optics,
  * same kernels, bit-identical results) without allocating: no hipMalloc,
  * hipHostMalloc or hipFree and no torch allocation.  Its device scratch
  * (spot state, random order, factor tables, sums and counters, launch
- * descriptors) is a file-scope static array of HG_STATIC_SCRATCH_BYTES,
- * of which each GPU the library runs on holds its own copy until the
- * process ends; the descriptors are staged through a static host area of
+ * descriptors) is counted against HG_STATIC_SCRATCH_BYTES and lies in a
+ * file-scope static array of one and a half times that size (the operand
+ * tables of wide grids take more than they count for), of which each GPU the
+ * library runs on holds its own copy until the process ends; the descriptors are staged through a static host area of
  * 1 MiB.  The first call on a device sets that device up (looks up its
  * copy of the array and creates one event).  Host-side planning still uses
  * ordinary C++ containers.

@@ -20,7 +20,10 @@
 // code `scratch` names a host-side stand-in, not the device array: the
 // device address of each GPU's copy comes from hipGetSymbolAddress, taken
 // once per device with that device current, and only that address is used.
-static __device__ __align__(256) char scratch[HG_STATIC_SCRATCH_BYTES];
+// The jobs' budgets are held to HG_STATIC_SCRATCH_BYTES; the half on top is the
+// reserve that their operand tables may take beyond.
+constexpr size_t kStaticArrayBytes = HG_STATIC_SCRATCH_BYTES + HG_STATIC_SCRATCH_BYTES / 2;
+static __device__ __align__(256) char scratch[kStaticArrayBytes];
 
 namespace {
 
@@ -202,8 +205,9 @@ hg_status static_scratch(StaticScratch** out) {
     HG_HIP(hipEventCreateWithFlags(&st->copied, hipEventDisableTiming));
     st->dev = static_cast<char*>(p);
     st->batch.adopt(st->dev + kStaticArenaOffset,
+                    kStaticArrayBytes - kStaticArenaOffset - kStaticTableBytes,
                     HG_STATIC_SCRATCH_BYTES - kStaticArenaOffset - kStaticTableBytes,
-                    st->dev + HG_STATIC_SCRATCH_BYTES - kStaticTableBytes, kStaticTableBytes,
+                    st->dev + kStaticArrayBytes - kStaticTableBytes, kStaticTableBytes,
                     st->host, kStaticTableBytes, st->copied);
     st->ready = true;
   }

@@ -10,18 +10,21 @@
 // Bound.  One hologram at 1152^2, N = 100, c = 1/16 (1296 tiles, five per
 // compute unit): a chain of about 4 us (launch, the reads of state and totals,
 // the update) in front of about 5 us of vector issue (38 cycles per 64 pairs
-// back, 44 forward), and the additions at the end.  What this form takes off
-// the per-pixel pass with deferred updates: the descriptor and job reads in
-// front of everything else (arguments in registers), the totals' trips to
-// memory (plain loads, shared in the L2), one of the tile's barriers with the
-// normalisation of all four waves' pixels by one wave, half of the addition
-// phase (one component per thread instead of two), the serial update on the
-// same SIMD for all blocks of a compute unit, and 16 VGPRs (60 instead of 76:
-// eight waves per SIMD instead of six).  Hologram time, before and after:
-// 1152^2, N = 100: 481 to 413 us (pass 14.2 to 12 us); 1920 x 1152 under the
-// pupil, N = 52, c = 1/8: 442 to 302 us; N = 300, c = 1/16: 1250 to 1051 us
-// (no hand-off, no update in the tail); mixed, N = 100: 502 to 405 us; 32
-// holograms of 1152^2 per batch: 8.54 to 7.32 ms.
+// back, 44 forward), and the additions at the end, which up to 64 spots bound
+// the pass.  What this form takes off the per-pixel pass with deferred updates:
+// the descriptor and job reads in front of everything else (arguments in
+// registers), the totals' trips to memory (plain loads, shared in the L2), one
+// of the tile's barriers with the normalisation of all four waves' pixels by
+// one wave, half of the addition phase (one component per thread instead of
+// two), 14 VGPRs (62 instead of 76: eight waves per SIMD instead of six), the
+// ends of the blocks one after another (wave priorities that fall along the
+// tile), and in large launches the starts of all but one tile in several and
+// the idle lanes of the forward phase.  Hologram time, before and after: 1152^2,
+// N = 100: 481 to 346 us (pass 14.2 to 10 us); 1920 x 1152 under the pupil, N =
+// 52, c = 1/8: 442 to 251 us; N = 300, c = 1/16: 1250 to 907 us (no hand-off, no
+// update in the tail); mixed, N = 100: 502 to 362 us; 32 holograms of 1152^2 per
+// batch: 8.54 to 5.47 ms; 64 mixed ones 19.0 to 11.5 ms.  (The full-grid passes'
+// own gains are in these.)
 #include <math.h>
 
 #include "device_common.hpp"

@@ -535,13 +535,16 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
   L.gen_offset = (L.grab_offset + s.iterations + 2 + kCounterStride - 1) / kCounterStride *
                  kCounterStride;
   j.counters_len = L.gen_offset + kGenCopies * kCounterStride;
-  size_t bytes = 0;
-  auto take = [&](size_t n) {
+  size_t bytes = 0, budget = 0;
+  auto count = [&](size_t n) { budget = align_up(budget, 256) + n; };
+  auto take_as = [&](size_t n, size_t counted) {
     bytes = align_up(bytes, 256);
     const size_t o = bytes;
     bytes += n;
+    count(counted);
     return o;
   };
+  auto take = [&](size_t n) { return take_as(n, n); };
   L.raw_inline = raw_inline && !s.spots_on_device;
   L.off_raw = L.raw_inline ? take(sizeof(double) * 4 * (size_t)s.N) : 0;
   L.off_sp = take(sizeof(SpotRec) * (size_t)s.N);
@@ -564,21 +567,26 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
   }
   if (!j.mixed || j.compressed) {  // exact fixed-point sums of the per-pixel passes
     j.acc_len = (int64_t)(acc_group_row0(s.N) + acc_groups) * acc_row_words(s.N);
-    L.off_acc = take(sizeof(unsigned long long) * (size_t)j.acc_len);
+    L.off_acc = take_as(sizeof(unsigned long long) * (size_t)j.acc_len,
+                        sizeof(double2) * (size_t)(kAccTotalRows * kAccRows + acc_groups) * s.N);
   }
   L.off_counters = take(sizeof(unsigned) * (size_t)j.counters_len);
   L.off_V = take(sizeof(double2) * (size_t)s.N *
                  (s.trace_host && s.iterations > 0 ? s.iterations : 1));
   if (L.separable) {
     const size_t ops = (size_t)j.mx_steps * 64;  // operand lanes per 16-row/column block
-    L.off_sepFc = take(sizeof(float) * 8 * ops * j.mx_cblocks);
-    L.off_sepGa = take(sizeof(float2) * 4 * ops * j.mx_rblocks);
+    const size_t fw = 32 * ops * j.mx_cblocks, gw = 32 * ops * j.mx_rblocks;
+    L.off_sepFc = take(fw);
+    L.off_sepGa = take_as(gw, 2 * gw);
     if (j.iter_tables) {
-      L.off_sepFs = take(sizeof(uint4) * 2 * ops * j.mx_cblocks);
-      L.off_sepFn = take(sizeof(uint4) * 2 * ops * j.mx_cblocks);
-      L.off_sepGv = take(sizeof(float2) * 4 * ops * j.mx_rblocks);
+      L.off_sepFs = take_as(fw, 0);
+      L.off_sepFn = take_as(fw, 0);
+      L.off_sepGv = take_as(gw, 0);
     }
+    count(fw);
+    count(gw);
   }
+  L.budget = align_up(budget, 256);
   L.bytes = align_up(bytes, 256);
   return L;
 }
@@ -1037,13 +1045,14 @@ hg_status Batch::build(const JobSpec* specs, int count, const TuneParams& tune,
       raw_off[i] = host_spot_bytes_;
       host_spot_bytes_ += sizeof(double) * 4 * (size_t)specs[i].N;
     }
-  size_t bytes = align_up(host_spot_bytes_, 256);
+  size_t bytes = align_up(host_spot_bytes_, 256), budget = bytes;
   int max_rounds = 0;
   perm_lds_ = true;
   for (int i = 0; i < count; ++i) {
     layouts_[i] = layout_job(specs[i], tp, status_dev, false);
     base_off[i] = bytes;
     bytes += layouts_[i].bytes;
+    budget += layouts_[i].budget;
     max_rounds = std::max(max_rounds, specs[i].iterations);
     const JobDev& j = layouts_[i].dev;
     if (j.compressed && !j.order_shared) {
@@ -1051,6 +1060,10 @@ hg_status Batch::build(const JobSpec* specs, int count, const TuneParams& tune,
     }
   }
   raw_base_ = 0;
+  if (arena_.adopted && budget > budget_)
+    return set_error(HG_ENOMEM, "the request needs " + std::to_string(budget) +
+                                    " bytes of static scratch in one region, which holds " +
+                                    std::to_string(budget_));
   HG_TRY(arena_.reserve(std::max<size_t>(bytes, 256)));
   for (int i = 0; i < count; ++i)
     jobs_[i] = bind_job(layouts_[i], specs[i], arena_.p + base_off[i],
@@ -1233,10 +1246,11 @@ hg_status Batch::custom_device(size_t size, char** dev) {
   return HG_OK;
 }
 
-void Batch::adopt(char* arena, size_t arena_bytes, char* table, size_t table_bytes, char* host,
-                  size_t host_bytes, hipEvent_t copied) {
+void Batch::adopt(char* arena, size_t arena_bytes, size_t budget, char* table, size_t table_bytes,
+                  char* host, size_t host_bytes, hipEvent_t copied) {
   release();
   arena_.adopt(arena, arena_bytes);
+  budget_ = budget;
   table_.adopt(table, table_bytes);
   staging_.adopt(host, host_bytes, copied);
   untimed_ = true;

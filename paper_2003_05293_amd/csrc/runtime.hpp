@@ -172,6 +172,12 @@ struct JobLayout {
          off_sepFs = 0, off_sepGa = 0, off_sepGv = 0, off_mxFc = 0, off_mxFn = 0, off_mxGa = 0, off_mxGv = 0,
          off_rows = 0;
   size_t bytes = 0;
+  // What the job counts for against a caller's limit (the static area, an
+  // engine's budget): bytes with one FP32 table per product and unpadded rows
+  // of exact sums.  On grids wider than high the split tables take more; the
+  // memory behind the limits has half of the limit in reserve for that
+  // (bytes <= 1.5 budget + 64 KiB).
+  size_t budget = 0;
   bool raw_inline = false;  // the job's own scratch holds a copy of its spot arrays
   int grab_offset = 0;      // the pass tile counters follow the group counters
   int gen_offset = 0;       // then the generation words of chained launches
@@ -307,8 +313,8 @@ class Batch {
   // host_bytes) guarded by `copied`.  Later builds allocate nothing (a
   // schedule that does not fit fails with HG_ENOMEM) and launches are
   // never timed.  Not for batches that use upload_custom.
-  void adopt(char* arena, size_t arena_bytes, char* table, size_t table_bytes, char* host,
-             size_t host_bytes, hipEvent_t copied);
+  void adopt(char* arena, size_t arena_bytes, size_t budget, char* table, size_t table_bytes,
+             char* host, size_t host_bytes, hipEvent_t copied);
   void release();
 
  private:
@@ -339,6 +345,7 @@ class Batch {
   Staging staging_;
   Staging custom_staging_;
   bool untimed_ = false;  // adopted memory: no timing events
+  size_t budget_ = 0;     // adopted memory: limit of the jobs' budgets
 };
 
 
