@@ -328,8 +328,10 @@ hg_status hg_batch_destroy(hg_batch *batch);
 typedef struct hg_engine hg_engine;
 
 typedef struct hg_engine_config {
-  size_t mem_budget_bytes;  /* device scratch for admitted requests (one
-                               pool allocated at creation)                   */
+  size_t mem_budget_bytes;  /* device scratch that requests are counted
+                               against (one pool allocated at creation, with
+                               a reserve for the operand tables of wide
+                               grids: half as much again, at most 272 MiB)   */
   int32_t max_slots;        /* holograms in flight at most (1 .. 4096)      */
   hg_tune tune;             /* launch geometry, 0 = default                 */
 } hg_engine_config;

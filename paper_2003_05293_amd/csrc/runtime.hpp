@@ -193,9 +193,10 @@ PassDesc iteration_desc(const JobDev& j, const JobLayout& L, int it, int index, 
 PixelSet all_pixels(int32_t M);
 
 // The launches of one iteration round (or of the final phase) of a set of
-// jobs: compressed passes (k_pass_batch), separable full-grid passes
-// (k_sep_pass, on the factor tables built by the prologue), direct full-grid final phases (k_backprop_batch) and the
-// passes of mixed-precision jobs (k_mx_pass).
+// jobs: compressed passes (k_pass_defer, k_pass_batch), separable full-grid
+// passes (k_sep_iter, k_sep_final, on the factor tables built by the prologue),
+// direct full-grid final phases (k_backprop_batch) and the passes of
+// mixed-precision jobs (k_pass_defer, k_pass_mx, k_mx_pass).
 struct LaunchSet {
   // per-pixel passes in two launches: jobs of one spot unit per wave (and
   // the shared-exponential form) in `pass`, wider jobs in `wide`, so that
