@@ -29,6 +29,7 @@ const char* last_error() { return g_err.c_str(); }
 // ----------------------------------------------------------------- staging --
 
 hg_status Staging::acquire(size_t bytes) {
+  refilled = pending;
   if (pending) {
     HG_HIP(hipEventSynchronize(done));
     pending = false;
@@ -58,6 +59,18 @@ hg_status Staging::acquire(size_t bytes) {
 // 346 us; the panel with 52 spots 256 to 252 us).
 hg_status Staging::copy(const std::vector<Piece>& pieces, bool mark, hipStream_t s) {
   constexpr size_t kUploadBytes = 256 << 10;
+  // A graph that the caller records would read the area again at each replay,
+  // whatever a later call has put there: refused where the area has served
+  // another call (hg_batch_create records graphs of its own).  Otherwise the
+  // event is a node of its own.
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (mark && hipStreamIsCapturing(s, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    cs = hipStreamCaptureStatusActive;
+  }
+  const bool recording = cs != hipStreamCaptureStatusNone;
+  if (recording && refilled)
+    return set_error(HG_EDEVICE, "the stream is being captured: use hg_batch_create");
   std::vector<Piece> small;
   for (const Piece& c : pieces) {
     if (!c.bytes) continue;
@@ -75,9 +88,9 @@ hg_status Staging::copy(const std::vector<Piece>& pieces, bool mark, hipStream_t
       u.dst[k] = reinterpret_cast<ulonglong2*>(small[i + k].dst);
       u.words[k] = (int32_t)(small[i + k].bytes / 16);
     }
-    launch_upload(u, n, mark && last ? done : nullptr, s);
+    launch_upload(u, n, mark && last && !recording ? done : nullptr, s);
   }
-  if (mark && small.empty()) return mark_copied(s);
+  if (mark && (small.empty() || recording)) return mark_copied(s);
   pending = pending || mark;
   return HG_OK;  // (a refused launch is reported by the check after the batch's launches)
 }

@@ -73,3 +73,26 @@ def test_tables_of_a_batch(count):
     for k in (0, count - 1):
         ref = hg.cswgs_device(g, OPTICS, on_gpu(spots[k]), 12, 0.25, k)
         assert np.array_equal(jobs[k].phi.cpu().numpy(), ref.cpu().numpy())
+
+
+def test_capture_by_the_caller_stays_refused():
+    """A replay would read the staging area as later calls have left it."""
+    import torch
+    print("[case] upload, captured stream", flush=True)
+    g = Grid(64, 48)
+    s = on_gpu(spot_cloud(1, 20, g))
+    st = torch.cuda.Stream()
+    phi = torch.empty(g.M, dtype=torch.float32, device="cuda")
+    with torch.cuda.stream(st):
+        hg.cswgs_device(g, OPTICS, s, 3, 0.25, 1, phi=phi, stream=st)
+    torch.cuda.synchronize()
+    ref = phi.clone()
+    with pytest.raises(Exception):
+        with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=st):
+            hg.cswgs_device(g, OPTICS, s, 3, 0.25, 1, phi=phi, stream=st)
+    phi.zero_()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        hg.cswgs_device(g, OPTICS, s, 3, 0.25, 1, phi=phi, stream=st)
+    torch.cuda.synchronize()
+    assert torch.equal(phi, ref)
