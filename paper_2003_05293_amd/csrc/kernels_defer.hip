@@ -21,7 +21,7 @@
 // tile), and in large launches the starts of all but one tile in several and
 // the idle lanes of the forward phase.  Hologram time, before and after: 1152^2,
 // N = 100: 481 to 346 us (pass 14.2 to 10 us); 1920 x 1152 under the pupil, N =
-// 52, c = 1/8: 442 to 251 us; N = 300, c = 1/16: 1250 to 907 us (no hand-off, no
+// 52, c = 1/8: 442 to 251 us; N = 300, c = 1/16: 1250 to 863 us (no hand-off, no
 // update in the tail); mixed, N = 100: 502 to 362 us; 32 holograms of 1152^2 per
 // batch: 8.54 to 5.47 ms; 64 mixed ones 19.0 to 11.5 ms.  (The full-grid passes'
 // own gains are in these.)
@@ -143,8 +143,14 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   __shared__ float2 sw[2][kWaves][kTile];
   __shared__ float4 px[kWaves][kTile];
   __shared__ float pui[kWaves][kTile];
-  // sums of the units (64 lanes each), or of the chains (cl.stride spots each)
-  __shared__ float2 red[kWaves * (CHAINS ? 2 : MAXU) * 64];
+  // sums of the units (64 lanes each), or of the chains (cl.stride spots each).
+  // With two units per wave they take the wave's own pixel rows, which it has
+  // read by then: 25.6 KB of LDS instead of 29.7, six blocks per compute unit
+  // instead of five (1920 x 1152, N = 300: 907 to 870 us per hologram).
+  __shared__ float2 red_own[MAXU > 1 ? 1 : kWaves * (CHAINS ? 2 : 1) * 64];
+  float2* red = MAXU > 1 ? reinterpret_cast<float2*>(&px[0][0]) : red_own;
+  static_assert(MAXU <= 2 && sizeof(px) == kWaves * 2 * 64 * sizeof(float2), "two units per row");
+  auto unit_at = [](int u) { return MAXU > 1 ? 128 * (u & (kWaves - 1)) + 64 * (u / kWaves) : 64 * u; };
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int N = h.N;
@@ -170,9 +176,10 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   // finish one after another, and the last ones run alone, where a wave issues
   // at half the rate.  Priorities that fall along the tile keep the blocks
   // level instead: all of them up to 256 spots, the last four of a compute
-  // unit in mixed precision and beyond 256 spots (whose blocks do not all fit
-  // at once).  1152^2, N = 100: 369 to 349 us (pass 10.75 to 10.05 us), mixed
-  // 372 to 362 us; N = 200, 2040 tiles 22.0 to 21.2 us; N = 512 50.5 to 48.8 us.
+  // unit in mixed precision, the last six (as many as fit at once) beyond 256
+  // spots (N = 300 with four 870, with six 863 us per hologram).  1152^2, N =
+  // 100: 369 to 349 us (pass 10.75 to 10.05 us), mixed 372 to 362 us; N = 200,
+  // 2040 tiles 22.0 to 21.2 us; N = 512 50.5 to 48.8 us.
   // In launches of several tiles per block the blocks' phases interleave the
   // better for it: 32 such holograms 5.65 to 5.48 ms, 64 mixed ones 12.1 to 11.5
   // ms.  Up to 64 spots the additions at the blocks' ends bound the pass, and
@@ -180,7 +187,7 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   // tiles per block, N = 16: 31.4 to 32.2 us a round): there only launches of many
   // tiles per block gain (eight, N = 52: 111 to 106 us; five, served: none).
   const bool paced = N > 64 || (CHAINS && plan.tiles >= 6 * plan.blocks);
-  const bool late = paced && (CHAINS || (MAXU == 1 && !MX) || lb + 4 * 256 >= plan.blocks);
+  const bool late = paced && (CHAINS || (MAXU == 1 && !MX) || lb + (MAXU > 1 ? 6 : 4) * 256 >= plan.blocks);
   int turn = 0;  // which waves take the odd rounds: in turn over the block's tiles
   // this thread's components of the tiles' sums (x = threadIdx.x + i kBlock)
   constexpr int kSums = 2 * MAXU;  // 2 N <= kSums kBlock
@@ -251,10 +258,11 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
       buf ^= 1;  // the next shares go to the other rows: one barrier is enough
     }
     if (!chains) {
+      if (MAXU > 1) asm volatile("" ::: "memory");  // the rows are read before they are rewritten
 #pragma unroll
       for (int k = 0; k < MAXU; ++k) {
         const int u = wave + k * kWaves;
-        if (u < lm.U) red[64 * u + lane] = make_float2(vr[k], vi[k]);
+        if (u < lm.U) red[unit_at(u) + lane] = make_float2(vr[k], vi[k]);
       }
     }
     if (paced) __builtin_amdgcn_s_setprio(0);
@@ -266,17 +274,18 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
       if (x >= 2 * N) break;
       const int n = x >> 1, part = x & 1;
       const int ch = n >> lm.lgL, gg = n & (Lg - 1);
-      const float* row = reinterpret_cast<const float*>(&red[64 * (ch << lm.lgS) + gg]) + part;
+      const int u0 = ch << lm.lgS;
+      const float* row = reinterpret_cast<const float*>(red + gg) + part;
       float s = 0.f;
       if (chains) {  // the two chains of a slice, then the slices
         const float* q = reinterpret_cast<const float*>(red) + x;
         for (int sl = 0; sl < (1 << cl.lgS); ++sl)
           s += q[2 * cl.stride * (2 * sl)] + q[2 * cl.stride * (2 * sl + 1)];
       } else if (R == 1) {
-        for (int sl = 0; sl < S; ++sl) s += row[2 * 64 * sl];
+        for (int sl = 0; sl < S; ++sl) s += row[2 * unit_at(u0 + sl)];
       } else {
         for (int sl = 0; sl < S; ++sl)
-          for (int rr = 0; rr < R; ++rr) s += row[2 * (64 * sl + (rr << lm.lgL))];
+          for (int rr = 0; rr < R; ++rr) s += row[2 * (unit_at(u0 + sl) + (rr << lm.lgL))];
       }
       sums[i] += (unsigned long long)llrint((double)s * scale);
     }

@@ -917,7 +917,7 @@ void LaunchSet::clear_sep_deferral() {
 // then forms the updated state once for all of them and adds their exact sums
 // to the totals once, and the next tile's pixel indices are on their way during
 // a tile's arithmetic.  Results do not depend on it.  The chip holds 2048 such
-// blocks (1280 of more than 256 spots).
+// blocks (1536 of more than 256 spots).
 // - From 2 kSpreadBlocks blocks on, T tiles per block (the same T for all passes
 //   of the launch): two and a half times what the chip holds keeps the launch's
 //   end even.  Measured with T = 1, 2, 4, 8, 16: 32 holograms of 1152^2 (41,472
