@@ -126,18 +126,21 @@ __host__ __device__ inline int32_t pupil_run(int32_t W, int32_t H, int32_t q, in
   return b >= a ? (int32_t)(b - a + 1) : 0;
 }
 
-// Row of pixel p < 2^26 on a grid of 2 <= W <= 8192 columns: p / W =
-// (p m) >> (32 + sh).  With 2^sh <= W < 2^(sh + 1) and m = ceil(2^(32 + sh) / W)
-// the excess m W - 2^(32 + sh) < W < 2^(sh + 1) times p stays below 2^(32 + sh).
+// Row of pixel p < 2^26 on a grid of W <= 8192 columns: with x = 2 p + 1 and
+// D = 2 W, p / W = x / D = (x m) >> (32 + sh) (rounded down).  With 2^sh <= D <
+// 2^(sh + 1) and m = ceil(2^(32 + sh) / D) the excess m D - 2^(32 + sh) < D <
+// 2^(sh + 1) times x < 2^27 stays below 2^(32 + sh), and x / D is at least 1 / D
+// away from the next whole number.  (Twice the pixel, so that one column, too, has
+// a multiplier of 32 bits.)
 struct RowDivisor {
   uint32_t m;
   int32_t sh;
 };
 inline RowDivisor row_divisor(int32_t W) {
+  const uint64_t D = 2 * (uint64_t)W;
   RowDivisor r{0u, 0};
-  while ((W >> (r.sh + 1)) != 0) ++r.sh;
-  const uint64_t top = uint64_t(1) << (32 + r.sh);
-  const uint64_t m = (top + (uint64_t)W - 1) / (uint64_t)W;
+  while ((D >> (r.sh + 1)) != 0) ++r.sh;
+  const uint64_t m = ((uint64_t(1) << (32 + r.sh)) + D - 1) / D;
   if (m >> 32) {  // W a power of two: half of both
     r.m = 0x80000000u;
     r.sh -= 1;

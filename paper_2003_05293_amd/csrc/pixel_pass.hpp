@@ -37,10 +37,10 @@ __device__ __forceinline__ PixCoord pixel_coord(int32_t p, int W, int H) {
   const int32_t j = p / W;
   return pixel_coord_ij(p - j * W, j, W, H);
 }
-// The same with the row from a multiplication: j = (p m) >> (32 + sh), m and
-// sh from row_divisor(W), exact for p < 2^26 (W, H <= 8192).
+// The same with the row from a multiplication: j = ((2 p + 1) m) >> (32 + sh), m
+// and sh from row_divisor(W), exact for p < 2^26 (W, H <= 8192).
 __device__ __forceinline__ PixCoord pixel_coord(int32_t p, int W, int H, uint32_t m, int sh) {
-  const int32_t j = (int32_t)(__umulhi((uint32_t)p, m) >> sh);
+  const int32_t j = (int32_t)(__umulhi(2u * (uint32_t)p + 1u, m) >> sh);
   return pixel_coord_ij(p - j * W, j, W, H);
 }
 

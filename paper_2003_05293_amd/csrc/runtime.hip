@@ -501,9 +501,8 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
   j.iter_tables = (L.separable && (s.iterations > 0 || s.hook)) ? 1 : 0;
   // compressed passes without an update of their own, where every pass up to
   // the final hologram takes deferred updates (a chained launch hands its
-  // updates over inside the launch instead; a grid of one column has no
-  // row divisor)
-  j.deferring = (j.compressed && s.phi && s.W >= 2 && !tp.chain_passes && !j.shared_e &&
+  // updates over inside the launch instead)
+  j.deferring = (j.compressed && s.phi && !tp.chain_passes && !j.shared_e &&
                  (j.mixed ? pass_units_per_wave(s.N) == 1 : L.separable && s.N <= kDeferMaxSpots))
                     ? 1
                     : 0;
@@ -656,13 +655,14 @@ JobDev bind_job(const JobLayout& L, const JobSpec& s, char* base, const double* 
 namespace {
 // Deferred updates.  Pass it of job j (1..I; I + 1 is the final hologram)
 // can apply the previous pass's update at its start, and so let that pass
-// stop after its sums: the compressed passes of deferring jobs and the
+// stop after its sums: the compressed passes of deferring jobs and the FP32
 // per-pixel ones of one spot unit per wave, the FP32 separable full-grid
 // passes and final hologram, and the mixed full-grid pass and final hologram
 // of a CS-WGS job, for N <= kPendMaxSpots (mixed: kBlock).
 bool pend_capable(const JobDev& j, const JobLayout& L, int it) {
   if (j.N > (j.mixed ? kBlock : kPendMaxSpots) || !j.sp_alt) return false;
-  if (j.compressed && it < j.iterations) return j.deferring || (j.defer_ok && !j.shared_e);
+  if (j.compressed && it < j.iterations)
+    return j.deferring || (!j.mixed && j.defer_ok && !j.shared_e);
   // mixed CS-WGS: the full-grid pass and the final hologram (the exact sums
   // of a mixed job are kept only with compressed passes)
   if (j.mixed) return j.compressed && (it == j.iterations || (it > j.iterations && j.phi));
