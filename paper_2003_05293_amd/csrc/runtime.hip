@@ -29,7 +29,7 @@ const char* last_error() { return g_err.c_str(); }
 // ----------------------------------------------------------------- staging --
 
 hg_status Staging::acquire(size_t bytes) {
-  refilled = pending;
+  refilled = refilled || pending;
   if (pending) {
     HG_HIP(hipEventSynchronize(done));
     pending = false;
@@ -60,9 +60,9 @@ hg_status Staging::acquire(size_t bytes) {
 hg_status Staging::copy(const std::vector<Piece>& pieces, bool mark, hipStream_t s) {
   constexpr size_t kUploadBytes = 256 << 10;
   // A graph that the caller records would read the area again at each replay,
-  // whatever a later call has put there: refused where the area has served
-  // another call (hg_batch_create records graphs of its own).  Otherwise the
-  // event is a node of its own.
+  // whatever a later call has put there: refused, every time, once the area has
+  // served another call (hg_batch_create records graphs of its own).  Otherwise
+  // the event is a node of its own.
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (mark && hipStreamIsCapturing(s, &cs) != hipSuccess) {
     (void)hipGetLastError();
@@ -105,7 +105,7 @@ void Staging::adopt(char* q, size_t n, hipEvent_t ev) {
   p = q;
   cap = n;
   done = ev;
-  pending = false;
+  pending = refilled = false;
   adopted = true;
 }
 
@@ -116,7 +116,7 @@ void Staging::release() {
   p = nullptr;
   cap = 0;
   done = nullptr;
-  pending = false;
+  pending = refilled = false;
   adopted = false;
 }
 

@@ -81,7 +81,7 @@ struct Staging {
   size_t cap = 0;
   hipEvent_t done = nullptr;
   bool pending = false;
-  bool refilled = false;  // acquired again after a copy
+  bool refilled = false;  // acquired again after a copy, at any time
   bool adopted = false;
   hg_status acquire(size_t bytes);             // waits for the previous copy, grows
   // Copies pieces of the area (offset, bytes) to the device; mark: records

@@ -96,3 +96,38 @@ def test_capture_by_the_caller_stays_refused():
         hg.cswgs_device(g, OPTICS, s, 3, 0.25, 1, phi=phi, stream=st)
     torch.cuda.synchronize()
     assert torch.equal(phi, ref)
+
+
+@pytest.mark.parametrize("entry", ["single", "batch"])
+def test_every_capture_by_the_caller_is_refused(entry):
+    """Also where the attempts follow each other without an ordinary call
+    between them, and again after one.  (An engine's step waits for its own
+    events first, which HIP refuses on a captured stream.)"""
+    import torch
+    print("[case] upload, captures in a row", entry, flush=True)
+    g = Grid(64, 48)
+    spots = spot_cloud(1, 20, g)
+    s = on_gpu(spots)
+    st = torch.cuda.Stream()
+    phi = torch.empty(g.M, dtype=torch.float32, device="cuda")
+    job = hg.DeviceJob.from_spots(g, OPTICS, spots, 3, 0.25, 1)
+    torch.cuda.synchronize()
+
+    def call():
+        if entry == "single":
+            hg.cswgs_device(g, OPTICS, s, 3, 0.25, 1, phi=phi, stream=st)
+        else:
+            hg.cswgs_batch([job], stream=st)
+
+    with torch.cuda.stream(st):
+        call()
+    torch.cuda.synchronize()
+    for attempts in (3, 2):
+        for k in range(attempts):
+            with pytest.raises(hg.HGError, match="HG_EDEVICE"):
+                with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=st):
+                    call()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(st):
+            call()
+        torch.cuda.synchronize()
