@@ -119,7 +119,11 @@ typedef struct hg_spots {
 
 /* Arithmetic of the iteration kernels (low bits of hg_params.flags and of
  * the flags argument of the single-step calls). */
-#define HG_PREC_FP32 0u   /* FP32 phases, sincos and sums                  */
+#define HG_PREC_FP32 0u   /* FP32 phases, sincos and sums; the products of
+                             the full-grid iteration passes on FP16 matrix
+                             cores, every FP32 operand as a sum of halves
+                             (23 to 36 bits of full scale), FP32 sums:
+                             HG_FULL_DIRECT keeps them per pixel in FP32 */
 #define HG_PREC_MIXED 1u  /* back-propagation as FP16 products
                              accumulated in FP32 (compressed passes: per
                              pixel, the cosines, sines and amplitudes of

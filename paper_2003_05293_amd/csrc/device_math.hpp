@@ -98,18 +98,22 @@ __device__ __forceinline__ uint32_t h2_bits(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, to_h2(lo, hi));
 }
 
-// (x, y) as a pair of halves, with hi[0], hi[1] their values.  The packed
+// (x, y) as a pair of halves, with v[0], v[1] their values.  The packed
 // word is opaque to the compiler: it could otherwise form a half's value a
 // second time from x's own expression, in a fused operation that rounds it
 // once instead of twice, and take the remainder of another half than the one
 // that is kept.
-__device__ __forceinline__ uint32_t pack_halves(float x, float y, float hi[2]) {
+__device__ __forceinline__ uint32_t pack_halves(float x, float y, float v[2]) {
   uint32_t bits = h2_bits(x, y);
-  asm volatile("" : "+v"(bits));
+  asm("" : "+v"(bits));
   const h2v_t h = __builtin_bit_cast(h2v_t, bits);
-  hi[0] = (float)h[0];
-  hi[1] = (float)h[1];
+  v[0] = (float)h[0];
+  v[1] = (float)h[1];
   return bits;
+}
+// Halves of whole numbers up to 2048 in magnitude (exact).
+__device__ __forceinline__ uint32_t whole_halves(float x, float y) {
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x, y));
 }
 
 __device__ __forceinline__ void sincos_turns(float t, float& s, float& c) {

@@ -230,9 +230,9 @@ __device__ void sep_tables_part(const JobDev& jb, int lb, int nb) {
       jb.sepFc[op_index4(col >> 4, n >> 1, KS, (col & 15) + 16 * (lgc + 1))] = (float)s;
       if (iter) {
         const double x = c * kSplitScale, y = s * kSplitScale;
-        float h[2];
-        const uint32_t hi = pack_halves((float)x, (float)y, h);
-        const uint32_t lo = h2_bits((float)(x - (double)h[0]), (float)(y - (double)h[1]));
+        const double xw = rint(x), yw = rint(y);
+        const uint32_t hi = whole_halves((float)xw, (float)yw);
+        const uint32_t lo = h2_bits((float)(x - xw), (float)(y - yw));
         const int cb = col >> 4, cl = col & 15, sb = n >> 4, nl = n & 15;
         uint32_t* fs = Fs + 8 * fc_index(cb, sb, S16, cl + 16 * (nl >> 2)) + (nl & 3);
         uint32_t* fn = Fn + 8 * fn_index(sb, cb, CB, nl + 16 * (cl >> 2)) + (cl & 3);

@@ -14,13 +14,24 @@
 //
 // The final hologram Phi = arg(B F) runs on v_mfma_f32_16x16x4_f32 (FP32
 // operands and sums).  The iteration's pass, whose products end in the mean
-// over all pixels, runs on v_mfma_f32_16x16x32_f16 with every FP32 operand
-// split into two FP16 parts, x = hi + lo with |x - hi - lo| <= 2^-22 |x| (F from
-// its FP64 value): hi hi + hi lo + lo hi, accumulated in FP32.  Three such
-// products cost 3/16 of the FP32 ones, and the sum over K is rounded once per
-// 32 terms instead of once per term.  Error of S against 64 bits, relative to
-// its rms, emulated for random phases: N = 16, 100, 300: 0.9, 1.2, 1.6 e-7,
-// where FP32 products give 1.2, 2.6, 4.3 e-7.
+// over all pixels, runs on v_mfma_f32_16x16x32_f16 with every operand scaled to
+// at most 2048 and split into a whole number and the half of the remainder, x =
+// hi + lo (F from its FP64 value), B with the half of what those two leave over
+// on top: rest hi + lo lo + lo hi + hi lo + hi hi for S, the last four for T,
+// accumulated in FP32.  These products cost 5/16 and 4/16 of the FP32 ones.
+//
+// Why whole numbers: the unit adds the eight products of a lane group aligned to
+// the largest of them and drops what lies below 2^-23 of that, towards zero
+// (then it adds the four groups, rounding each time).  With floating high parts a
+// weak spot beside a strong one thus came out short by up to 2^-24 of the strong
+// amplitude, at every pixel alike.  Products of whole numbers up to 2048 and sums
+// of eight of them are exact; those of the low parts lose 2^-35 of full scale.
+// What is left, relative to full scale (the largest |C_n|, or 1 for F and u): hi +
+// lo is off by up to 2^-24 (a third of that rms; for an FP32 number between 1/2 and
+// 1: 2^-25), B by 2^-36.  Fields of one pass against 64 bits, error of a spot
+// relative to its own field, rms, for amplitudes spread over 0, 1, 2, 3 and 5 decades (640 x
+// 480, N = 100, 24 draws): 2.9, 4.2, 12, 44 and 99 e-8; FP32 products 2.9, 4.7, 15,
+// 55 and 110 e-8; halves of the floating form 2.9, 4.3, 19, 106 and 252 e-8.
 #include <math.h>
 
 #include "device_common.hpp"
@@ -227,11 +238,19 @@ __device__ __forceinline__ f4_t mfma16(const u4_t& a, const u4_t& b, const f4_t&
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8_t, a),
                                                 __builtin_bit_cast(h8_t, b), c, 0, 0, 0);
 }
-// (x, y) as a pair of halves and the pair of what the halves leave over.
-__device__ __forceinline__ void split_pair(float x, float y, uint32_t& hi, uint32_t& lo) {
-  float h[2];
-  hi = pack_halves(x, y, h);
-  lo = h2_bits(x - h[0], y - h[1]);
+// (x, y), at most 2048 in magnitude, as halves of whole numbers, of the
+// remainders, and of what those leave over.
+struct Split {
+  uint32_t hi, lo, rest;
+};
+__device__ __forceinline__ Split split_pair(float x, float y) {
+  Split s;
+  const float xw = rintf(x), yw = rintf(y);
+  float l[2];
+  s.hi = whole_halves(xw, yw);
+  s.lo = pack_halves(x - xw, y - yw, l);
+  s.rest = h2_bits(fmaf(l[0], -1.f, x - xw), fmaf(l[1], -1.f, y - yw));
+  return s;
 }
 // For half pairs (re, im) of z: the pair of -i z, (im, -re).
 __device__ __forceinline__ u4_t times_minus_i(const u4_t& v) {
@@ -248,19 +267,20 @@ __device__ __forceinline__ u4_t times_i_conj(const u4_t& v) {
   return r;
 }
 
-// Power of two s with s max_n |C_n| (larger part) in [1024, 2048): the split
-// halves of s B and, F carrying a factor kSplitScale, those of F stay normal
-// numbers down to 2^-22 of the largest, and u = S / |S| does not depend on s.
-// Every wave forms it from the staged coefficients.
+// Power of two s with s max_n |C_n| <= 2048 (and at least 724): then the parts
+// of s B stay within 2048, and u = S / |S| does not depend on s.  Every wave
+// forms it from the staged coefficients.
 __device__ __forceinline__ float coef_scale(const float2* cs, int N, int lane) {
   float m = 0.f;
   for (int n = lane; n < N; n += 64) m = fmaxf(m, fmaxf(fabsf(cs[n].x), fabsf(cs[n].y)));
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  const int e = (int)(__builtin_bit_cast(uint32_t, m) >> 23);  // biased exponent
-  // 2^(10 - (e - 127)); zero, subnormal, infinite or NaN: as they are
+  const uint32_t bits = __builtin_bit_cast(uint32_t, m);
+  int e = (int)(bits >> 23);  // biased exponent of the largest part
+  // zero, subnormal, infinite or NaN: as they are
   if (e == 0 || e == 255) return 1.f;
-  const int se = 127 + 10 - (e - 127);
+  if ((bits & 0x7fffffu) >= 0x3504f3u) ++e;  // |C| <= sqrt(2) m may reach the next power
+  const int se = 127 + 10 - (e - 127);       // 2^(10 - (e - 127))
   return __builtin_bit_cast(float, (uint32_t)(se < 1 ? 1 : se > 254 ? 254 : se) << 23);
 }
 
@@ -289,25 +309,26 @@ __device__ __forceinline__ void it_mma(const ItOps& o, const float2* cs, float s
   const int n0 = 16 * s + 4 * lg;
   const float gx[4] = {o.g02[0], o.g13[0], o.g02[2], o.g13[2]};
   const float gy[4] = {o.g02[1], o.g13[1], o.g02[3], o.g13[3]};
-  u4_t rh, rl;
+  u4_t rh, rl, rm;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const float cx = cs[n0 + q].x * scale, cy = cs[n0 + q].y * scale;
     const float br = fmaf(cx, gx[q], -cy * gy[q]), bi = fmaf(cx, gy[q], cy * gx[q]);
-    uint32_t hi, lo;
-    split_pair(br, -bi, hi, lo);
-    rh[q] = hi;
-    rl[q] = lo;
+    const Split b = split_pair(br, -bi);
+    rh[q] = b.hi;
+    rl[q] = b.lo;
+    rm[q] = b.rest;
   }
-  const u4_t ih = times_i_conj(rh), il = times_i_conj(rl);
+  const u4_t re[3] = {rm, rl, rh};
+  const u4_t im[3] = {times_i_conj(rm), times_i_conj(rl), times_i_conj(rh)};
 #pragma unroll
-  for (int t = 0; t < kSepCB; ++t) {
-    sr[t] = mfma16(rl, o.f[t][0], sr[t]);
-    si[t] = mfma16(il, o.f[t][0], si[t]);
-    sr[t] = mfma16(rh, o.f[t][1], sr[t]);
-    si[t] = mfma16(ih, o.f[t][1], si[t]);
-    sr[t] = mfma16(rh, o.f[t][0], sr[t]);
-    si[t] = mfma16(ih, o.f[t][0], si[t]);
+  for (int p = 0; p < 5; ++p) {  // rest hi, lo lo, lo hi, hi lo, hi hi
+    const int k = (p + 1) / 2, l = p & 1;
+#pragma unroll
+    for (int t = 0; t < kSepCB; ++t) {
+      sr[t] = mfma16(re[k], o.f[t][l], sr[t]);
+      si[t] = mfma16(im[k], o.f[t][l], si[t]);
+    }
   }
 }
 
@@ -343,11 +364,11 @@ __device__ __forceinline__ void it_forward(const JobDev& jb, const u4_t (*ua)[2]
 #pragma unroll
   for (int t = 0; t < kSepCB; ++t)
 #pragma unroll
-    for (int p = 0; p < 3; ++p)  // lo hi, hi lo, hi hi
+    for (int p = 0; p < 4; ++p)  // lo lo, lo hi, hi lo, hi hi
 #pragma unroll
       for (int k = 0; k < R; ++k) {
-        tr[k] = mfma16(ua[t][p == 0], f[t][k][p == 1], tr[k]);
-        ti[k] = mfma16(ub[t][p == 0], f[t][k][p == 1], ti[k]);
+        tr[k] = mfma16(ua[t][p < 2], f[t][k][(p & 1) == 0], tr[k]);
+        ti[k] = mfma16(ub[t][p < 2], f[t][k][(p & 1) == 0], ti[k]);
       }
 #pragma unroll
   for (int k = 0; k < R; ++k) {
@@ -371,15 +392,14 @@ __device__ __forceinline__ void it_forward(const JobDev& jb, const u4_t (*ua)[2]
 // waves but C_n until the tile's partial sums meet.
 //
 // Bound: at 1152^2, N = 100 (648 tiles, 2.5 per compute unit) the matrix cores
-// need about 4 us (FP32 products: 18 us on the busiest SIMD), forming and
-// splitting B about 2 us; the rest is the chain of launch, the pending update
+// need about 6 us (FP32 products: 18 us on the busiest SIMD), forming and
+// splitting B about 3 us; the rest is the chain of launch, the pending update
 // and the operand loads in front of them.  FP32 products with the descriptor
 // read in front of the loads, and these split products with their start as
-// arguments: 1152^2, N = 100: 33.4 and 16.6 us; 1000 x 777, N = 52: 15.6 and
-// 9.9 us; 1920 x 1152, N = 300: 133 and 58 us; 32 holograms of 1152^2 in one
-// launch: 717 and 358 us.  Fields of one pass against 64 bits, rms over the
-// spots of eight cases: 2.66e-8 and 2.60e-8 of |V|; WGS holograms of 24 drawn
-// sizes: 5.06e-7 and 5.01e-7.
+// arguments: 1152^2, N = 100: 33.4 and 18.5 us; 1000 x 777, N = 52: 15.6 and
+// 10.8 us; 1920 x 1152, N = 300: 133 and 67 us; 32 holograms of 1152^2 in one
+// launch: 717 and 460 us.  (Halves of the floating form without the products rest hi
+// and lo lo: 16.0, 9.7, 59 and 416 us, less precise beside strong spots.)
 __global__ __launch_bounds__(kBlock, 3) void k_sep_iter(
     const SpotRec* st, const unsigned long long* tot, const float2* ga, const void* f, uint32_t nst,
     uint32_t wh, const SepDesc* __restrict__ descs, const JobDev* __restrict__ jobs) {
@@ -453,10 +473,9 @@ __global__ __launch_bounds__(kBlock, 3) void k_sep_iter(
           uy *= wt;
         }
       }
-      uint32_t hi, lo;
-      split_pair(ux, uy, hi, lo);
-      us[wave][0][4 * lg + r][16 * t + lr] = hi;
-      us[wave][1][4 * lg + r][16 * t + lr] = lo;
+      const Split u = split_pair(ux, uy);
+      us[wave][0][4 * lg + r][16 * t + lr] = u.hi;
+      us[wave][1][4 * lg + r][16 * t + lr] = u.lo;
     }
   // (the wave's own rows: its LDS accesses complete in order)
   __builtin_amdgcn_wave_barrier();

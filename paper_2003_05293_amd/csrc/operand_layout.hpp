@@ -30,8 +30,8 @@ __device__ __forceinline__ int64_t ga_index4(int blk, int step, int steps, int l
   return (((int64_t)blk * (steps >> 2) + (step >> 2)) * 32 + lane32) * 4 + (step & 3);
 }
 
-// Split FP16 operands of the iteration pass: F times 2^kSplitBits as a sum of
-// two halves.  Tables in the layout of the mixed-precision operands below,
+// Split FP16 operands of the iteration pass: F times 2^kSplitBits as a whole
+// number and a half of the remainder.  Tables in the layout of the mixed-precision operands below,
 // with two 16-byte words per lane (the hi pairs, then the lo pairs).
 constexpr int kSplitBits = 11;
 constexpr float kSplitScale = 2048.0f;
