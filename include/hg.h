@@ -239,10 +239,9 @@ hg_status hg_cswgs_ex(const hg_grid *grid, const hg_optics *optics,
  * same kernels, bit-identical results) without allocating: no hipMalloc,
  * hipHostMalloc or hipFree and no torch allocation.  Its device scratch
  * (spot state, random order, factor tables, sums and counters, launch
- * descriptors) is counted against HG_STATIC_SCRATCH_BYTES and lies in a
- * file-scope static array of one and a half times that size (the operand
- * tables of wide grids take more than they count for), of which each GPU the
- * library runs on holds its own copy until the process ends; the descriptors are staged through a static host area of
+ * descriptors) is a file-scope static array of HG_STATIC_SCRATCH_BYTES,
+ * of which each GPU the library runs on holds its own copy until the
+ * process ends; the descriptors are staged through a static host area of
  * 1 MiB.  The first call on a device sets that device up (looks up its
  * copy of the array and creates one event).  Host-side planning still uses
  * ordinary C++ containers.
@@ -332,10 +331,8 @@ hg_status hg_batch_destroy(hg_batch *batch);
 typedef struct hg_engine hg_engine;
 
 typedef struct hg_engine_config {
-  size_t mem_budget_bytes;  /* device scratch that requests are counted
-                               against (one pool allocated at creation, with
-                               a reserve for the operand tables of wide
-                               grids: half as much again, at most 272 MiB)   */
+  size_t mem_budget_bytes;  /* device scratch for admitted requests (one
+                               pool allocated at creation)                   */
   int32_t max_slots;        /* holograms in flight at most (1 .. 4096)      */
   hg_tune tune;             /* launch geometry, 0 = default                 */
 } hg_engine_config;

@@ -20,10 +20,7 @@
 // code `scratch` names a host-side stand-in, not the device array: the
 // device address of each GPU's copy comes from hipGetSymbolAddress, taken
 // once per device with that device current, and only that address is used.
-// The jobs' budgets are held to HG_STATIC_SCRATCH_BYTES; the half on top is the
-// reserve that their operand tables may take beyond.
-constexpr size_t kStaticArrayBytes = HG_STATIC_SCRATCH_BYTES + HG_STATIC_SCRATCH_BYTES / 2;
-static __device__ __align__(256) char scratch[kStaticArrayBytes];
+static __device__ __align__(256) char scratch[HG_STATIC_SCRATCH_BYTES];
 
 namespace {
 
@@ -205,9 +202,8 @@ hg_status static_scratch(StaticScratch** out) {
     HG_HIP(hipEventCreateWithFlags(&st->copied, hipEventDisableTiming));
     st->dev = static_cast<char*>(p);
     st->batch.adopt(st->dev + kStaticArenaOffset,
-                    kStaticArrayBytes - kStaticArenaOffset - kStaticTableBytes,
                     HG_STATIC_SCRATCH_BYTES - kStaticArenaOffset - kStaticTableBytes,
-                    st->dev + kStaticArrayBytes - kStaticTableBytes, kStaticTableBytes,
+                    st->dev + HG_STATIC_SCRATCH_BYTES - kStaticTableBytes, kStaticTableBytes,
                     st->host, kStaticTableBytes, st->copied);
     st->ready = true;
   }
@@ -380,6 +376,7 @@ hg_status hg_cswgs_static(const hg_grid* grid, const hg_optics* optics, const hg
                        params->seed, params->flags, phi_dev, nullptr, &spec));
   HG_TRY(hg::apply_lut(params->lut, params->gray_dev, &spec));
   if (!phi_dev) return set_error(HG_EINVAL, "phi_dev must be non-NULL");
+  spec.fixed_scratch = true;
   StaticScratch* st = nullptr;
   HG_TRY(static_scratch(&st));
   std::lock_guard<std::mutex> lk(st->mu);

@@ -98,6 +98,7 @@ hg_status spec_from_job(const hg_job& j, hg::JobSpec* out) {
   HG_TRY(hg::make_spec(&j.grid, &j.optics, &j.spots, j.iterations, j.compression, j.seed,
                        j.flags, j.phi_dev, nullptr, out));
   HG_TRY(hg::apply_lut(j.lut, j.gray_dev, out));
+  out->fixed_scratch = true;
   return hg::attach_shared_order(out);
 }
 
@@ -168,14 +169,8 @@ hg_status hg_engine_create(const hg_engine_config* cfg, hg_engine** out) {
   if (cfg->tune.full_block_cap > 0) e->tp.full_block_cap = cfg->tune.full_block_cap;
   if (cfg->tune.subset_block_cap > 0) e->tp.subset_block_cap = cfg->tune.subset_block_cap;
   e->tp.pass_form = cfg->tune.pass_form;
-  // the reserve of the budget's largest job (JobLayout::budget; at most one
-  // more F table of 4096 spots by 8192 columns), where memory allows it
-  const size_t spare = std::min(e->budget / 2, (size_t)272 << 20) + (64 << 10);
-  if (e->pool.reserve(e->budget + spare) != HG_OK) {
-    (void)hipGetLastError();
-    HG_TRY(e->pool.reserve(e->budget));
-  }
-  e->alloc.reset(e->pool.cap);
+  HG_TRY(e->pool.reserve(e->budget));
+  e->alloc.reset(e->budget);
   HG_TRY(e->status.reserve(1));
   HG_HIP(hipMemset(e->status.p, 0, sizeof(int32_t)));
   e->slots.resize(e->max_slots);
@@ -189,8 +184,7 @@ hg_status hg_engine_submit(hg_engine* e, const hg_job* job, uint64_t* ticket) {
   Request r;
   HG_TRY(spec_from_job(*job, &r.spec));
   std::lock_guard<std::mutex> lk(e->mu);
-  const hg::JobLayout need = hg::layout_job(r.spec, e->tp, nullptr, true);
-  if (need.budget > e->budget || need.bytes > e->pool.cap)
+  if (hg::layout_job(r.spec, e->tp, nullptr, true).budget > e->budget)
     return set_error(HG_ENOMEM, "request needs more scratch than the engine's whole budget");
   if (!r.spec.spots_on_device) {
     const int N = r.spec.N;

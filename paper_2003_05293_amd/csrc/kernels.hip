@@ -202,7 +202,8 @@ __device__ void setup_part(const JobDev& jb, int lb, int nb) {
 // and, for the iteration pass,
 //   Fs  back-propagation B operand, col 16 cb + l%16, spots 16 s + 4 g + q,
 //       and Fn  forward B operand, spot 16 sb + l%16, columns 16 cb + 4 g + q:
-//       half pairs (re, im) of the two parts of 2^kSplitBits F;
+//       half pairs (re, im) of the two parts of 2^kSplitBits F (Fn: where the
+//       job has one);
 //   Gv  G_n(row) for spot 16 sb + l%16 and rows 16 rb + 4 g + r (V sums).
 __device__ void sep_tables_part(const JobDev& jb, int lb, int nb) {
   const int W = jb.W, H = jb.H, N = jb.N;
@@ -235,11 +236,13 @@ __device__ void sep_tables_part(const JobDev& jb, int lb, int nb) {
         const uint32_t lo = h2_bits((float)(x - xw), (float)(y - yw));
         const int cb = col >> 4, cl = col & 15, sb = n >> 4, nl = n & 15;
         uint32_t* fs = Fs + 8 * fc_index(cb, sb, S16, cl + 16 * (nl >> 2)) + (nl & 3);
-        uint32_t* fn = Fn + 8 * fn_index(sb, cb, CB, nl + 16 * (cl >> 2)) + (cl & 3);
         fs[0] = hi;
         fs[4] = lo;
-        fn[0] = hi;
-        fn[4] = lo;
+        if (Fn) {
+          uint32_t* fn = Fn + 8 * fn_index(sb, cb, CB, nl + 16 * (cl >> 2)) + (cl & 3);
+          fn[0] = hi;
+          fn[4] = lo;
+        }
       }
     } else {
       const int64_t kk = k - nF;
@@ -623,9 +626,9 @@ __device__ void pass_block(const PassCtx& a, unsigned* grab, bool has_pre = fals
         }
       // a deferring pass adds into a row of its total set, others into
       // their tile's group
-      const int row = a.defer ? a.tot_row * acc_rows(N) + tile % acc_rows(N)
-                              : acc_group_row0(N) + tile / a.plan.group_size;
-      acc_add(a.acc, N, a.plan.shift, row, n, acc);
+      const int row = a.defer ? (a.tot_row * acc_rows(N) + tile % acc_rows(N)) * acc_row_words(N)
+                              : acc_group_at(N, tile / a.plan.group_size);
+      acc_add(a.acc + row, a.plan.shift, n, acc);
     }
     if (threadIdx.x == 0) {
       done[ndone++] = tile;
@@ -780,7 +783,7 @@ __device__ void pass_block_e(const PassCtx& a, unsigned* grab) {
     }
     // the tile's partials: spot n_lo + lane of each wave
     if (lane < cnt)
-      acc_add(a.acc, N, a.plan.shift, acc_group_row0(N) + tile / a.plan.group_size, n_lo + lane,
+      acc_add(a.acc + acc_group_at(N, tile / a.plan.group_size), a.plan.shift, n_lo + lane,
               rede[wave][lane]);
     if (threadIdx.x == 0) {
       done[ndone++] = tile;

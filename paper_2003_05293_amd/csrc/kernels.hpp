@@ -77,9 +77,12 @@ constexpr int kAccWideSpots = 257;
 __host__ __device__ inline int acc_rows(int N) {
   return N < kAccWideSpots ? kAccRows : kAccRowsWide;
 }
-// Words per set, and the row of group 0.
+// Words per set, and the place of group g's row behind the sets (not padded: a
+// group has one adder at a time).
 __host__ __device__ inline int acc_set_words(int N) { return acc_rows(N) * acc_row_words(N); }
-__host__ __device__ inline int acc_group_row0(int N) { return kAccTotalRows * acc_rows(N); }
+__host__ __device__ inline int acc_group_at(int N, int g) {
+  return kAccTotalRows * acc_set_words(N) + g * N * kAccSpotWords;
+}
 // Fixed-point scale of the exact sums of a pass over `pixels` pixels: every
 // term has magnitude <= 1, so |sum| * 2^shift <= 2^62.
 int sum_shift(int64_t pixels);
@@ -184,16 +187,16 @@ struct JobDev {
   float2* partial;     // [max pass tiles][N] (mixed-precision passes)
   double2* gpart;      // [max pass groups][N] (mixed-precision passes)
   // exact fixed-point sums of the FP32 passes: the sets of pass
-  // totals, then row acc_group_row0(N) + g for group g; per spot a (re, im) two's-
+  // totals, then a row per group (acc_group_at); per spot a (re, im) two's-
   // complement pair at the start of an entry of kAccSpotWords words; zero
   // between passes, except a total that a deferred update leaves for the
   // next pass
-  unsigned long long* acc;  // [acc_group_row0(N) + max pass groups][acc_row_words(N)]
+  unsigned long long* acc;  // [acc_group_at(N, max pass groups)]
   int64_t acc_len;
   unsigned* counters;  // [max pass groups + 1] group and pass counters, kCounterStride apart
   unsigned* grab;      // [iterations + 2] tile counters of the passes (PassDesc::grab_slot)
   int32_t counters_len;  // counters, grab and gen, zeroed by the setup
-  unsigned* gen;       // [kGenCopies * kCounterStride] passes completed in a chained launch
+  unsigned* gen;       // [kGenCopies * kCounterStride] passes completed (chained launches only)
   int32_t trace;       // V is [iterations][N] instead of [N]
   double2* V;
   int32_t* status;     // sticky status word of the caller's stream
@@ -212,7 +215,8 @@ struct JobDev {
   // of the iteration pass (iter_tables), split into two FP16 parts each
   int32_t iter_tables; // 0: no full-grid iteration (RS): these are not built
   uint4* sepFs;        // [Wp/16][Np/16][64] x 2  back-propagation B operand
-  uint4* sepFn;        // [Np/16][Wp/16][64] x 2  forward B operand
+  uint4* sepFn;        // [Np/16][Wp/16][64] x 2  forward B operand (jobs of fixed
+                       // scratch: null, from sepFs)
   float4* sepGv;       // [Hp/16][Np/16][64] x 2 float4: G for the V sums
   // mixed-precision matrix-core passes: FP16 / FP32 tables
   uint4* mxFc;         // [Wp/16][Np/16][64] x 4 half2   (back-propagation operand)
@@ -417,6 +421,7 @@ struct SepHead {
   const uint4* fs = nullptr;
   int32_t N = 0, S16 = 0, W = 0, H = 0, tiles_x = 0, tiles_y = 0;
   int32_t job = 0;                          // index of the job in the launch's table
+  bool own_fn = true;                       // JobDev::sepFn, the same for all jobs of the launch
 };
 void launch_sep_pass(const JobDev* jobs, const SepDesc* descs, int ndesc, int total_blocks,
                      bool final, int max_steps, const SepHead& head, hipStream_t s);

@@ -441,7 +441,8 @@ __global__ __launch_bounds__(kBlock, 3) void k_mx_pass(const JobDev* __restrict_
           v.y += red[w][threadIdx.x].y;
         }
         if (d.defer)
-          acc_add(jb.acc, N, d.plan.shift, d.tot_row * acc_rows(N) + lb % acc_rows(N), n, v);
+          acc_add(jb.acc + (d.tot_row * acc_rows(N) + lb % acc_rows(N)) * acc_row_words(N),
+                  d.plan.shift, n, v);
         else
           store_dev(jb.partial + (int64_t)lb * N + n, v);
       }

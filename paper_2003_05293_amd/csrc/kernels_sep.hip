@@ -332,21 +332,49 @@ __device__ __forceinline__ void it_mma(const ItOps& o, const float2* cs, float s
   }
 }
 
+// The F operand of the forward product, spot l % 16 and columns 4 (l / 16) + q of
+// a 16-column block, from the table of the back-propagation (column l % 16,
+// spots 4 (l / 16) + q), for jobs without one of its own: lane l reads the four
+// spots 4 (l % 16 / 4) + q of column 4 (l / 16) + l % 4, and the four lanes of a
+// quad exchange rows and columns.  Costs 0.8 us per pass at 1000 x 777, N = 52 (10.8
+// to 11.6 us), nothing measurable where blocks fill the chip.
+__device__ __forceinline__ int quad_source(int lane) {
+  return 4 * (lane >> 4) + (lane & 3) + 16 * ((lane & 15) >> 2);
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_perm(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+__device__ __forceinline__ u4_t quad_transpose(const u4_t& v, int lane) {
+  constexpr int kXor1 = 0xb1, kXor2 = 0x4e;  // lanes (1, 0, 3, 2) and (2, 3, 0, 1)
+  const bool b0 = lane & 1, b1 = lane & 2;
+  // (every lane takes part in an exchange: they stand outside the selections)
+  const u4_t x = {quad_perm<kXor1>(v[1]), quad_perm<kXor1>(v[0]), quad_perm<kXor1>(v[3]),
+                  quad_perm<kXor1>(v[2])};
+  const u4_t a = {b0 ? x[0] : v[0], b0 ? v[1] : x[1], b0 ? x[2] : v[2], b0 ? v[3] : x[3]};
+  const u4_t y = {quad_perm<kXor2>(a[2]), quad_perm<kXor2>(a[3]), quad_perm<kXor2>(a[0]),
+                  quad_perm<kXor2>(a[1])};
+  return u4_t{b1 ? y[0] : a[0], b1 ? y[1] : a[1], b1 ? a[2] : y[2], b1 ? a[3] : y[3]};
+}
+
 // T = U conj(F)^T for R 16-spot blocks starting at sb0 and the wave's 16
 // rows, then the wave's partial V_n = sum_j conj(G_n(j)) T[j][n] of those
 // spots into red (LDS).
-template <int R>
-__device__ __forceinline__ void it_forward(const JobDev& jb, const u4_t (*ua)[2],
+template <int R, bool OWN_FN>
+__device__ __forceinline__ void it_forward(const JobDev& jb, const u4_t* Fs, const u4_t (*ua)[2],
                                            const u4_t (*ub)[2], float2* red, int sb0, int rb,
                                            int tx, int S16, int CB, int lane) {
   const int lr = lane & 15, lg = lane >> 4;
-  const HG_GLOBAL u4_t* Fn = as_global(reinterpret_cast<const u4_t*>(jb.sepFn));
+  const u4_t* Fn = reinterpret_cast<const u4_t*>(jb.sepFn);
   u4_t f[kSepCB][R][2];
 #pragma unroll
   for (int t = 0; t < kSepCB; ++t)
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-      const HG_GLOBAL u4_t* fp = Fn + 2 * fn_index(sb0 + k, kSepCB * tx + t, CB, lane);
+      const int cb = kSepCB * tx + t;
+      const HG_GLOBAL u4_t* fp =
+          OWN_FN ? as_global(Fn) + 2 * fn_index(sb0 + k, cb, CB, lane)
+                 : as_global(Fs) + 2 * fc_index(cb, sb0 + k, S16, quad_source(lane));
       f[t][k][0] = fp[0];
       f[t][k][1] = fp[1];
     }
@@ -361,6 +389,15 @@ __device__ __forceinline__ void it_forward(const JobDev& jb, const u4_t (*ua)[2]
   f4_t tr[R], ti[R];
 #pragma unroll
   for (int k = 0; k < R; ++k) tr[k] = ti[k] = f4_t{0.f, 0.f, 0.f, 0.f};
+  if (!OWN_FN) {
+#pragma unroll
+    for (int t = 0; t < kSepCB; ++t)
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        f[t][k][0] = quad_transpose(f[t][k][0], lane);
+        f[t][k][1] = quad_transpose(f[t][k][1], lane);
+      }
+  }
 #pragma unroll
   for (int t = 0; t < kSepCB; ++t)
 #pragma unroll
@@ -400,6 +437,8 @@ __device__ __forceinline__ void it_forward(const JobDev& jb, const u4_t (*ua)[2]
 // 10.8 us; 1920 x 1152, N = 300: 133 and 67 us; 32 holograms of 1152^2 in one
 // launch: 717 and 460 us.  (Halves of the floating form without the products rest hi
 // and lo lo: 16.0, 9.7, 59 and 416 us, less precise beside strong spots.)
+// OWN_FN: the forward product has a table of its own.
+template <bool OWN_FN>
 __global__ __launch_bounds__(kBlock, 3) void k_sep_iter(
     const SpotRec* st, const unsigned long long* tot, const float2* ga, const void* f, uint32_t nst,
     uint32_t wh, const SepDesc* __restrict__ descs, const JobDev* __restrict__ jobs) {
@@ -494,19 +533,19 @@ __global__ __launch_bounds__(kBlock, 3) void k_sep_iter(
   // the next launch reads the set)
   const int CB = jb.mx_cblocks;
   const int grp = h.lb / d.plan.group_size;
-  const int row =
-      d.defer ? d.tot_row * acc_rows(N) + h.lb % acc_rows(N) : acc_group_row0(N) + grp;
-  unsigned long long* out = jb.acc + (int64_t)row * acc_row_words(N);
+  unsigned long long* out =
+      jb.acc + (d.defer ? (d.tot_row * acc_rows(N) + h.lb % acc_rows(N)) * acc_row_words(N)
+                        : acc_group_at(N, grp));
   // T carries kSplitScale twice (exact powers of two)
   const double unit = ldexp(1.0, d.plan.shift - 2 * kSplitBits);
   for (int b0 = 0; b0 < S16; b0 += kSepRed / 16) {
     const int b1 = min(S16, b0 + kSepRed / 16);
     int sb = b0;
-    for (; sb + 4 <= b1; sb += 4) it_forward<4>(jb, ua, ub, red[wave], sb, rb, h.tx, S16, CB, lane);
+    for (; sb + 4 <= b1; sb += 4) it_forward<4, OWN_FN>(jb, Fs, ua, ub, red[wave], sb, rb, h.tx, S16, CB, lane);
     switch (b1 - sb) {
-      case 3: it_forward<3>(jb, ua, ub, red[wave], sb, rb, h.tx, S16, CB, lane); break;
-      case 2: it_forward<2>(jb, ua, ub, red[wave], sb, rb, h.tx, S16, CB, lane); break;
-      case 1: it_forward<1>(jb, ua, ub, red[wave], sb, rb, h.tx, S16, CB, lane); break;
+      case 3: it_forward<3, OWN_FN>(jb, Fs, ua, ub, red[wave], sb, rb, h.tx, S16, CB, lane); break;
+      case 2: it_forward<2, OWN_FN>(jb, Fs, ua, ub, red[wave], sb, rb, h.tx, S16, CB, lane); break;
+      case 1: it_forward<1, OWN_FN>(jb, Fs, ua, ub, red[wave], sb, rb, h.tx, S16, CB, lane); break;
       default: break;
     }
     __syncthreads();
@@ -581,8 +620,11 @@ void launch_sep_pass(const JobDev* jobs, const SepDesc* descs, int ndesc, int to
   if (final)
     hipLaunchKernelGGL(k_sep_final, grid, dim3(kBlock), shmem, s, head.st, head.tot, head.ga,
                        head.fc, nst, wh, descs, j);
+  else if (head.own_fn)
+    hipLaunchKernelGGL(k_sep_iter<true>, grid, dim3(kBlock), shmem, s, head.st, head.tot, head.ga,
+                       (const void*)head.fs, nst, wh, descs, j);
   else
-    hipLaunchKernelGGL(k_sep_iter, grid, dim3(kBlock), shmem, s, head.st, head.tot, head.ga,
+    hipLaunchKernelGGL(k_sep_iter<false>, grid, dim3(kBlock), shmem, s, head.st, head.tot, head.ga,
                        (const void*)head.fs, nst, wh, descs, j);
 }
 

@@ -70,11 +70,10 @@ __device__ __forceinline__ void load_recs_dev(const SpotRec* sp, int N, SpotRec*
 // sum overflows) and added with device-scope integer atomics: integer
 // addition is associative, so the sums do not depend on the order in which
 // tiles, groups or blocks arrive.  Rows: the sets of pass totals (acc_rows(N)
-// each), then row acc_group_row0(N) + g = group g.
-__device__ __forceinline__ void acc_add(unsigned long long* acc, int N, int shift, int row, int n,
-                                        float2 v) {
+// each), then the groups'.
+__device__ __forceinline__ void acc_add(unsigned long long* row, int shift, int n, float2 v) {
   const double scale = ldexp(1.0, shift);
-  unsigned long long* p = acc + row * acc_row_words(N) + n * kAccSpotWords;
+  unsigned long long* p = row + n * kAccSpotWords;
   atomicAdd(p, (unsigned long long)llrint((double)v.x * scale));
   atomicAdd(p + 1, (unsigned long long)llrint((double)v.y * scale));
 }
@@ -91,7 +90,7 @@ __device__ __forceinline__ unsigned long long take_dev(unsigned long long* p) {
 __device__ bool tail_group(const PassCtx& a, int g, int* flag) {
   for (int k = threadIdx.x; k < 2 * a.N; k += kBlock) {
     const int64_t e = (int64_t)(k >> 1) * kAccSpotWords + (k & 1);  // spot k / 2, part k % 2
-    const unsigned long long v = take_dev(a.acc + (acc_group_row0(a.N) + g) * acc_row_words(a.N) + e);
+    const unsigned long long v = take_dev(a.acc + acc_group_at(a.N, g) + e);
     atomicAdd(a.acc + a.tot_row * acc_set_words(a.N) + e, v);
   }
   return arrive_last(&a.counters[a.plan.ngroups * kCounterStride], (unsigned)a.plan.ngroups, flag);

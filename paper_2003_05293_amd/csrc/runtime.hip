@@ -546,7 +546,7 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
   L.grab_offset = (std::max(max_groups, acc_groups) + 1) * kCounterStride;
   L.gen_offset = (L.grab_offset + s.iterations + 2 + kCounterStride - 1) / kCounterStride *
                  kCounterStride;
-  j.counters_len = L.gen_offset + kGenCopies * kCounterStride;
+  j.counters_len = L.gen_offset + (tp.chain_passes ? kGenCopies * kCounterStride : 0);
   size_t bytes = 0, budget = 0;
   auto count = [&](size_t n) { budget = align_up(budget, 256) + n; };
   auto take_as = [&](size_t n, size_t counted) {
@@ -578,11 +578,12 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
     L.off_gpart = take(sizeof(double2) * (size_t)max_groups * s.N);
   }
   if (!j.mixed || j.compressed) {  // exact fixed-point sums of the per-pixel passes
-    j.acc_len = (int64_t)(acc_group_row0(s.N) + acc_groups) * acc_row_words(s.N);
+    j.acc_len = acc_group_at(s.N, acc_groups);
     L.off_acc = take_as(sizeof(unsigned long long) * (size_t)j.acc_len,
                         sizeof(double2) * (size_t)(kAccTotalRows * kAccRows + acc_groups) * s.N);
   }
-  L.off_counters = take(sizeof(unsigned) * (size_t)j.counters_len);
+  L.off_counters = take_as(sizeof(unsigned) * (size_t)j.counters_len,
+                           sizeof(unsigned) * (size_t)(L.gen_offset + kGenCopies * kCounterStride));
   L.off_V = take(sizeof(double2) * (size_t)s.N *
                  (s.trace_host && s.iterations > 0 ? s.iterations : 1));
   if (L.separable) {
@@ -592,7 +593,8 @@ JobLayout layout_job(const JobSpec& s, const TuneParams& tp, int32_t* status_dev
     L.off_sepGa = take_as(gw, 2 * gw);
     if (j.iter_tables) {
       L.off_sepFs = take_as(fw, 0);
-      L.off_sepFn = take_as(fw, 0);
+      L.own_fn = !s.fixed_scratch;
+      if (L.own_fn) L.off_sepFn = take_as(fw, 0);
       L.off_sepGv = take_as(gw, 0);
     }
     count(fw);
@@ -632,14 +634,14 @@ JobDev bind_job(const JobLayout& L, const JobSpec& s, char* base, const double* 
                                       : nullptr;
   j.counters = reinterpret_cast<unsigned*>(base + L.off_counters);
   j.grab = j.counters + L.grab_offset;
-  j.gen = j.counters + L.gen_offset;
+  j.gen = j.counters_len > L.gen_offset ? j.counters + L.gen_offset : nullptr;
   j.V = reinterpret_cast<double2*>(base + L.off_V);
   if (L.separable) {
     j.sepFc = reinterpret_cast<float*>(base + L.off_sepFc);
     j.sepGa = reinterpret_cast<float2*>(base + L.off_sepGa);
     if (j.iter_tables) {
       j.sepFs = reinterpret_cast<uint4*>(base + L.off_sepFs);
-      j.sepFn = reinterpret_cast<uint4*>(base + L.off_sepFn);
+      if (L.own_fn) j.sepFn = reinterpret_cast<uint4*>(base + L.off_sepFn);
       j.sepGv = reinterpret_cast<float4*>(base + L.off_sepGv);
     }
   }
@@ -787,6 +789,7 @@ SepHead sep_head(const JobDev& j, const SepDesc& d) {
   h.ga = j.sepGa;
   h.fc = j.sepFc;
   h.fs = j.sepFs;
+  h.own_fn = j.sepFn != nullptr;
   h.N = j.N;
   h.S16 = j.mx_steps;
   h.W = j.W;
@@ -1047,6 +1050,11 @@ hg_status Batch::build(const JobSpec* specs, int count, const TuneParams& tune,
                        int32_t* status_dev, bool allow_chain) {
   TuneParams tp = tune;
   tp.chain_passes = tune.chain_passes && allow_chain && count == 1 && chain_fits(specs[0], tune);
+  // (its generation words may be what an adopted area has no room for: same bits
+  // without)
+  if (tp.chain_passes && arena_.adopted &&
+      layout_job(specs[0], tp, status_dev, false).bytes > arena_.cap)
+    tp.chain_passes = false;
   specs_.assign(specs, specs + count);
   jobs_.assign(count, JobDev{});
   layouts_.resize(count);
@@ -1073,10 +1081,10 @@ hg_status Batch::build(const JobSpec* specs, int count, const TuneParams& tune,
     }
   }
   raw_base_ = 0;
-  if (arena_.adopted && budget > budget_)
+  if (arena_.adopted && budget > arena_.cap)
     return set_error(HG_ENOMEM, "the request needs " + std::to_string(budget) +
                                     " bytes of static scratch in one region, which holds " +
-                                    std::to_string(budget_));
+                                    std::to_string(arena_.cap));
   HG_TRY(arena_.reserve(std::max<size_t>(bytes, 256)));
   for (int i = 0; i < count; ++i)
     jobs_[i] = bind_job(layouts_[i], specs[i], arena_.p + base_off[i],
@@ -1259,11 +1267,10 @@ hg_status Batch::custom_device(size_t size, char** dev) {
   return HG_OK;
 }
 
-void Batch::adopt(char* arena, size_t arena_bytes, size_t budget, char* table, size_t table_bytes,
-                  char* host, size_t host_bytes, hipEvent_t copied) {
+void Batch::adopt(char* arena, size_t arena_bytes, char* table, size_t table_bytes, char* host,
+                  size_t host_bytes, hipEvent_t copied) {
   release();
   arena_.adopt(arena, arena_bytes);
-  budget_ = budget;
   table_.adopt(table, table_bytes);
   staging_.adopt(host, host_bytes, copied);
   untimed_ = true;

@@ -118,6 +118,7 @@ struct JobSpec {
   uint32_t precision = HG_PREC_FP32;
   bool full_direct = false;   // full-grid passes with the per-pixel kernels
   bool hook = false;          // single-pass entry point (any pixel set up to W*H)
+  bool fixed_scratch = false; // the scratch comes out of a limit that the caller set
   float* phi = nullptr;       // output hologram (device)
   double* trace_host = nullptr;
   // SLM output: the final pass also writes the gray image (device)
@@ -174,11 +175,13 @@ struct JobLayout {
          off_rows = 0;
   size_t bytes = 0;
   // What the job counts for against a caller's limit (the static area, an
-  // engine's budget): bytes with one FP32 table per product and unpadded rows
-  // of exact sums.  On grids wider than high the split tables take more; the
-  // memory behind the limits has half of the limit in reserve for that
-  // (bytes <= 1.5 budget + 64 KiB).
+  // engine's budget): bytes with one FP32 table per product, G for both, unpadded
+  // rows of exact sums and the words of a chained launch.  Never less than bytes
+  // for jobs of fixed scratch that are not chained: these do without Fn, and below
+  // 257 spots the padding of the sums' rows (at most 30 x 48 bytes) is less than
+  // the chain's words (2 KiB).
   size_t budget = 0;
+  bool own_fn = false;      // the iteration pass's forward product has its own table
   bool raw_inline = false;  // the job's own scratch holds a copy of its spot arrays
   int grab_offset = 0;      // the pass tile counters follow the group counters
   int gen_offset = 0;       // then the generation words of chained launches
@@ -315,8 +318,8 @@ class Batch {
   // host_bytes) guarded by `copied`.  Later builds allocate nothing (a
   // schedule that does not fit fails with HG_ENOMEM) and launches are
   // never timed.  Not for batches that use upload_custom.
-  void adopt(char* arena, size_t arena_bytes, size_t budget, char* table, size_t table_bytes,
-             char* host, size_t host_bytes, hipEvent_t copied);
+  void adopt(char* arena, size_t arena_bytes, char* table, size_t table_bytes, char* host,
+             size_t host_bytes, hipEvent_t copied);
   void release();
 
  private:
@@ -347,7 +350,6 @@ class Batch {
   Staging staging_;
   Staging custom_staging_;
   bool untimed_ = false;  // adopted memory: no timing events
-  size_t budget_ = 0;     // adopted memory: limit of the jobs' budgets
 };
 
 
