@@ -333,8 +333,8 @@ __host__ __device__ int pass_e_width(int N);
 // max_units the largest two-phase unit count of the others.
 void launch_pass_batch(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,
                        int max_units, int e_width, hipStream_t s);
-// Compressed passes of `deferring` jobs: N <= kDeferMaxSpots (FP32) or
-// kBlock (mixed: FP16 back-propagation products accumulated in FP32).  With
+// Compressed passes of `deferring` jobs: N <= kBlock or, wide (FP32 only), N <=
+// kDeferMaxSpots (mixed: FP16 back-propagation products accumulated in FP32).  With
 // one descriptor, `head` holds what the start of its pass reads.  large: the
 // launch fills the chip several times over (any value gives the same bits).
 constexpr int kDeferMaxSpots = 512;
@@ -347,7 +347,7 @@ struct PassHead {
   int32_t job = 0;                          // index of the job in the launch's table
 };
 void launch_pass_defer(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,
-                       int max_spots, bool mixed, bool large, const PassHead& head,
+                       bool wide, bool mixed, bool large, const PassHead& head,
                        hipStream_t s);
 // Compressed passes of the other mixed-precision jobs (more than one spot
 // unit per wave); descs and units as for launch_pass_batch.

@@ -364,7 +364,7 @@ __global__ __launch_bounds__(kBlock, MAXU > 1 ? 4 : 6) void k_pass_defer(
 }  // namespace
 
 void launch_pass_defer(const JobDev* jobs, const PassDesc* descs, int ndesc, int total_blocks,
-                       int max_spots, bool mixed, bool large, const PassHead& head,
+                       bool wide, bool mixed, bool large, const PassHead& head,
                        hipStream_t s) {
   if (ndesc <= 0 || total_blocks <= 0) return;
   const dim3 grid(total_blocks), block(kBlock);
@@ -375,7 +375,7 @@ void launch_pass_defer(const JobDev* jobs, const PassDesc* descs, int ndesc, int
 #define HG_LAUNCH(U, M, C)                                                                       \
   hipLaunchKernelGGL((k_pass_defer<U, M, C>), grid, block, 0, s, head.st, head.tot, head.perm,   \
                      start, head.P, head.count, nss, wh, head.row_div.m, descs, j)
-  if (max_spots > kBlock) HG_LAUNCH(2, false, false);
+  if (wide) HG_LAUNCH(2, false, false);
   else if (mixed && large) HG_LAUNCH(1, true, true);
   else if (mixed) HG_LAUNCH(1, true, false);
   else if (large) HG_LAUNCH(1, false, true);

@@ -817,15 +817,17 @@ PassHead pass_head(const JobDev& j, const PassDesc& d) {
 }
 }  // namespace
 
+void LaunchSet::DeferSet::add(const JobDev& j, PassDesc d) {
+  if (list.empty()) head = pass_head(j, d);
+  list.push_back(d);
+  blocks += d.plan.blocks;
+}
+
 void LaunchSet::add_iteration(const JobDev& j, const JobLayout& L, int it, int index) {
   const bool sub = j.compressed && it < j.iterations;
   if (sub && j.deferring) {
-    const PassDesc d = iteration_desc(j, L, it, index, j.mixed ? mxp_blocks : dfr_blocks);
-    std::vector<PassDesc>& list = j.mixed ? mxp : dfr;
-    if (list.empty()) (j.mixed ? mxp_head : dfr_head) = pass_head(j, d);
-    list.push_back(d);
-    (j.mixed ? mxp_blocks : dfr_blocks) += d.plan.blocks;
-    if (!j.mixed) dfr_spots = std::max(dfr_spots, j.N);
+    DeferSet& set = j.mixed ? mxp : pass_units_per_wave(j.N) == 1 ? dfr : dfw;
+    set.add(j, iteration_desc(j, L, it, index, set.blocks));
     return;
   }
   if (j.mixed && sub) {  // per-pixel compressed pass, FP16 back-propagation
@@ -903,11 +905,12 @@ void LaunchSet::add_final(const JobDev& j, const JobLayout& L, int index) {
 }
 
 size_t LaunchSet::bytes() const {
-  return align_up(sizeof(PassDesc) * dfr.size(), 256) +
+  return align_up(sizeof(PassDesc) * dfr.list.size(), 256) +
+         align_up(sizeof(PassDesc) * dfw.list.size(), 256) +
          align_up(sizeof(PassDesc) * pass.size(), 256) + align_up(sizeof(PassDesc) * wide.size(), 256) +
          align_up(sizeof(SepDesc) * sep.size(), 256) +
          align_up(sizeof(BackDesc) * back.size(), 256) + align_up(sizeof(MxDesc) * mx.size(), 256) +
-         align_up(sizeof(PassDesc) * mxp.size(), 256) + align_up(sizeof(PassDesc) * mxw.size(), 256);
+         align_up(sizeof(PassDesc) * mxp.list.size(), 256) + align_up(sizeof(PassDesc) * mxw.size(), 256);
 }
 
 void LaunchSet::clear_sep_deferral() {
@@ -934,28 +937,47 @@ void LaunchSet::clear_sep_deferral() {
 //   the first of every pass, not of the launch, and some end late (two passes
 //   of 1296 tiles, N = 200: 28.9 us as they are, 30.0 us; six, N = 100: 42.8 us,
 //   43.3 with 2048, 41.2 with 4096 blocks).
-void LaunchSet::spread_tiles() {
+void LaunchSet::DeferSet::spread(bool wide) {
   constexpr int kSpreadBlocks = 5120, kFewBlocks = 4096, kOneBlocks = 2048;
-  auto spread = [](std::vector<PassDesc>& list, int* total, int spots, bool* large) {
-    const int64_t all = *total, T = all / kSpreadBlocks;
-    *large = T >= 2;
-    const int64_t keep = *large ? (all + T - 1) / T : list.size() > 1 ? kFewBlocks
-                                 : spots > kBlock ? all : kOneBlocks;
-    if (keep >= all) return;
-    *total = 0;
-    for (PassDesc& d : list) {
-      d.block_begin = *total;
-      d.plan.blocks = (int)(*large ? (d.plan.blocks + T - 1) / T
-                                   : (d.plan.blocks * keep + all - 1) / all);
-      *total += d.plan.blocks;
-    }
-  };
-  spread(dfr, &dfr_blocks, dfr_spots, &dfr_large);
-  spread(mxp, &mxp_blocks, kBlock, &mxp_large);
+  const int64_t all = blocks, T = all / kSpreadBlocks;
+  large = T >= 2;
+  const int64_t keep = large ? (all + T - 1) / T : list.size() > 1 ? kFewBlocks
+                               : wide ? all : kOneBlocks;
+  if (keep >= all) return;
+  blocks = 0;
+  for (PassDesc& d : list) {
+    d.block_begin = blocks;
+    d.plan.blocks = (int)(large ? (d.plan.blocks + T - 1) / T
+                                : (d.plan.blocks * keep + all - 1) / all);
+    blocks += d.plan.blocks;
+  }
+}
+
+// Passes of up to and of more than 256 spots in one round: the narrow ones join
+// the wide launch, behind its longer blocks, and fill its end, up to 20480 blocks
+// of them.  Beyond that a launch of their own, whose kernel holds eight blocks per
+// compute unit instead of six and sums by chains, is the better one.  The bits are the
+// same.  Batches of 1152^2, 12 iterations, joined and apart: one hologram of 100 spots
+// and one of 300 505 and 565 us; 7 and 1 1040 and 1096; 15 and 1 (19,440 narrow
+// blocks) 1739 and 1744; 31 and 1 (40,176) 3169 and 3084; 16 of 150 and 16 of 300
+// 6398 and 6422.  (In the order of the jobs, the wide blocks last: 541, 1140, 2027, 3831
+// and 6672.)
+void LaunchSet::join_defer() {
+  constexpr int kJoinBlocks = 20480;
+  if (dfw.list.empty() || dfr.blocks >= kJoinBlocks) return;
+  for (PassDesc& d : dfr.list) {
+    d.block_begin += dfw.blocks;
+    dfw.list.push_back(d);
+  }
+  dfw.blocks += dfr.blocks;
+  dfr = DeferSet{};
 }
 
 size_t LaunchSet::stage(char* host, char* dev) {
-  spread_tiles();
+  join_defer();
+  dfr.spread(false);
+  dfw.spread(true);
+  mxp.spread(false);
   size_t o = 0;
   auto put = [&](const void* src, size_t n) {
     const size_t at = o;
@@ -963,13 +985,13 @@ size_t LaunchSet::stage(char* host, char* dev) {
     o = align_up(o + n, 256);
     return dev + at;
   };
-  d_dfr = reinterpret_cast<const PassDesc*>(put(dfr.data(), sizeof(PassDesc) * dfr.size()));
+  for (DeferSet* set : {&dfr, &dfw, &mxp})
+    set->dev = reinterpret_cast<const PassDesc*>(put(set->list.data(), sizeof(PassDesc) * set->list.size()));
   d_pass = reinterpret_cast<const PassDesc*>(put(pass.data(), sizeof(PassDesc) * pass.size()));
   d_wide = reinterpret_cast<const PassDesc*>(put(wide.data(), sizeof(PassDesc) * wide.size()));
   d_sep = reinterpret_cast<const SepDesc*>(put(sep.data(), sizeof(SepDesc) * sep.size()));
   d_back = reinterpret_cast<const BackDesc*>(put(back.data(), sizeof(BackDesc) * back.size()));
   d_mx = reinterpret_cast<const MxDesc*>(put(mx.data(), sizeof(MxDesc) * mx.size()));
-  d_mxp = reinterpret_cast<const PassDesc*>(put(mxp.data(), sizeof(PassDesc) * mxp.size()));
   d_mxw = reinterpret_cast<const PassDesc*>(put(mxw.data(), sizeof(PassDesc) * mxw.size()));
   return o;
 }
@@ -984,11 +1006,11 @@ const char* pass_name(const std::vector<PassDesc>& a, const std::vector<PassDesc
 }  // namespace
 
 const char* LaunchSet::pass_only_name() const {
-  const bool fp32 = !pass.empty() || !wide.empty(), mixed = !mxp.empty() || !mxw.empty();
-  if ((int)!dfr.empty() + (int)fp32 + (int)mixed != 1 || !sep.empty() || !back.empty() ||
-      !mx.empty())
+  const bool fp32 = !pass.empty() || !wide.empty(), mixed = !mxp.list.empty() || !mxw.empty();
+  const bool deferring = !dfr.list.empty() || !dfw.list.empty();
+  if ((int)deferring + (int)fp32 + (int)mixed != 1 || !sep.empty() || !back.empty() || !mx.empty())
     return nullptr;
-  return !dfr.empty() ? "k_pass_subset" : fp32 ? pass_name(pass, wide) : "k_mxp_subset";
+  return deferring ? "k_pass_subset" : fp32 ? pass_name(pass, wide) : "k_mxp_subset";
 }
 
 void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
@@ -1000,11 +1022,12 @@ void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
     run(sep_final ? "k_sep_final" : "k_sep_pass", [&] {
       launch_sep_pass(jobs, d_sep, (int)sep.size(), sep_blocks, sep_final, sep_steps, sep_start, s);
     });
-  if (!dfr.empty())
-    run("k_pass_subset", [&] {
-      launch_pass_defer(jobs, d_dfr, (int)dfr.size(), dfr_blocks, dfr_spots, false, dfr_large,
-                        dfr_head, s);
-    });
+  for (const DeferSet* set : {&dfr, &dfw})
+    if (!set->list.empty())
+      run("k_pass_subset", [&] {
+        launch_pass_defer(jobs, set->dev, (int)set->list.size(), set->blocks, set == &dfw, false,
+                          set->large, set->head, s);
+      });
   if (!pass.empty())
     run(pass_name(pass, {}),
         [&] { launch_pass_batch(jobs, d_pass, (int)pass.size(), pass_blocks, 1, e_width, s); });
@@ -1015,10 +1038,10 @@ void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
   if (!back.empty())
     run("k_backprop_phi",
         [&] { launch_backprop_batch(jobs, d_back, (int)back.size(), back_blocks, s); });
-  if (!mxp.empty())
+  if (!mxp.list.empty())
     run("k_mxp_subset", [&] {
-      launch_pass_defer(jobs, d_mxp, (int)mxp.size(), mxp_blocks, kBlock, true, mxp_large, mxp_head,
-                        s);
+      launch_pass_defer(jobs, mxp.dev, (int)mxp.list.size(), mxp.blocks, false, true, mxp.large,
+                        mxp.head, s);
     });
   if (!mxw.empty())
     run("k_mxp_subset",

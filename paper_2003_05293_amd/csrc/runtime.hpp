@@ -205,12 +205,19 @@ struct LaunchSet {
   // per-pixel passes in two launches: jobs of one spot unit per wave (and
   // the shared-exponential form) in `pass`, wider jobs in `wide`, so that
   // every job runs in the same kernel form alone and in any batch
-  // (the passes of `deferring` jobs in launches of their own: dfr, FP32, and
-  // mxp, mixed)
-  std::vector<PassDesc> dfr;
-  int dfr_blocks = 0, dfr_spots = 0;
-  bool dfr_large = false, mxp_large = false;  // several tiles per block
-  PassHead dfr_head, mxp_head;  // of the first pass of each
+  // (the passes of `deferring` jobs in launches of their own: FP32 of one spot
+  // unit per wave, FP32 of two, and mixed)
+  struct DeferSet {
+    std::vector<PassDesc> list;
+    int blocks = 0;
+    bool large = false;             // several tiles per block
+    PassHead head;                  // of the first pass
+    const PassDesc* dev = nullptr;  // device copy, set by stage()
+    void add(const JobDev& j, PassDesc d);
+    void spread(bool wide);
+  };
+  DeferSet dfr, dfw, mxp;
+  void join_defer();  // the narrow passes into the wide launch, where they are few
   std::vector<PassDesc> pass;
   int pass_blocks = 0;
   int e_width = 0;  // widest shared-exponential form among the passes (0: none)
@@ -225,20 +232,16 @@ struct LaunchSet {
   std::vector<MxDesc> mx;
   int mx_blocks = 0, mx_steps = 0, mx_full = 0;
   int mx_mode = kMxIterate;
-  // compressed passes of mixed-precision jobs (per-pixel, FP16
-  // back-propagation): deferring jobs in mxp, wider jobs in mxw
-  std::vector<PassDesc> mxp;
-  int mxp_blocks = 0;
+  // compressed passes of the mixed-precision jobs that do not defer (per-pixel,
+  // FP16 back-propagation)
   std::vector<PassDesc> mxw;
   int mxw_blocks = 0, mxw_units = 1;
   // device copies, set by stage()
-  const PassDesc* d_dfr = nullptr;
   const PassDesc* d_pass = nullptr;
   const PassDesc* d_wide = nullptr;
   const SepDesc* d_sep = nullptr;
   const BackDesc* d_back = nullptr;
   const MxDesc* d_mx = nullptr;
-  const PassDesc* d_mxp = nullptr;
   const PassDesc* d_mxw = nullptr;
 
   void add_iteration(const JobDev& j, const JobLayout& L, int it, int index);
@@ -247,8 +250,8 @@ struct LaunchSet {
   // pixels, no update).
   void add_forward_mx(const JobDev& j, const JobLayout& L, int index);
   bool empty() const {
-    return dfr.empty() && pass.empty() && wide.empty() && sep.empty() && back.empty() && mx.empty() &&
-           mxp.empty() && mxw.empty();
+    return dfr.list.empty() && dfw.list.empty() && pass.empty() && wide.empty() && sep.empty() &&
+           back.empty() && mx.empty() && mxp.list.empty() && mxw.empty();
   }
   // Timing name of the set's per-pixel pass launch when that is all the set
   // launches, else nullptr.
@@ -257,8 +260,6 @@ struct LaunchSet {
   // Copies the descriptors into host staging at `host` and points the
   // device copies at `dev` (same offsets); returns the bytes used.
   size_t stage(char* host, char* dev);
-  // Several tiles per block where the launch has many blocks (stage() does it).
-  void spread_tiles();
   // Makes the set's separable passes update in their own tails.
   void clear_sep_deferral();
   // Launches the set's kernels.  `capture`: no timing.
