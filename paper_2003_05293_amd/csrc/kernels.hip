@@ -1020,8 +1020,8 @@ __global__ __launch_bounds__(kGrayThreads) void k_phase_to_gray(const float* __r
 // Small tables and spot arrays from pinned host memory: the bytes cross the
 // host link either way, and a copy command costs its engine's start and the
 // hand-over to the next kernel on top.  Bound by one read over the link (3 to
-// 4 us for 1 to 40 KB).  Random superposition of 16 spots on 256 x 256: 31.2
-// to 28 us; 16 served holograms, a table per round: 3.01 to 2.71 ms.  The loads
+// 4 us for 1 to 40 KB).  Random superposition of 16 spots on 256 x 256: 32.1
+// to 28.5 us; 16 served holograms, a table per round: 3.01 to 2.71 ms.  The loads
 // are of system scope: nothing in a cache stands in for what the host wrote.
 __global__ __launch_bounds__(kBlock) void k_upload(UploadSegs u) {
   const int s = blockIdx.y, k = blockIdx.x * kBlock + threadIdx.x;

@@ -77,8 +77,8 @@ constexpr int kAccWideSpots = 257;
 __host__ __device__ inline int acc_rows(int N) {
   return N < kAccWideSpots ? kAccRows : kAccRowsWide;
 }
-// Words per set, and the place of group g's row behind the sets (not padded: a
-// group has one adder at a time).
+// Words per set, and the place of group g's row behind the sets (packed, so that a
+// job takes no more than it counts for against a caller's limit).
 __host__ __device__ inline int acc_set_words(int N) { return acc_rows(N) * acc_row_words(N); }
 __host__ __device__ inline int acc_group_at(int N, int g) {
   return kAccTotalRows * acc_set_words(N) + g * N * kAccSpotWords;
@@ -176,10 +176,9 @@ struct JobDev {
   double pitch_mm, lambda_mm, focal_mm;
   SpotPtrs in;         // spot inputs (device)
   SpotRec* sp;         // [N] iteration state
-  SpotRec* sp_alt;     // [N] second state buffer of deferred updates (FP32 jobs)
-  int32_t defer_ok;    // deferred updates allowed: an FP32 job of one spot unit
-                       // per wave (N <= 256), whose passes run in the one-unit
-                       // launch of each round
+  SpotRec* sp_alt;     // [N] second state buffer of deferred updates
+  int32_t defer_ok;    // one spot unit per wave (N <= 256): where such an FP32 job
+                       // is not `deferring`, its per-pixel passes can defer too
   float2* coef;        // [N] C_n = A_n e^{i 2 pi th_n}, kept with the state
   uint32_t* tab;       // [6 << h] Feistel tables (compressed only)
   int32_t* perm;       // [P] random pixel order (compressed only)

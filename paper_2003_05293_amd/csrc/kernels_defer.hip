@@ -20,10 +20,10 @@
 // ends of the blocks one after another (wave priorities that fall along the
 // tile), and in large launches the starts of all but one tile in several and
 // the idle lanes of the forward phase.  Hologram time, before and after: 1152^2,
-// N = 100: 481 to 346 us (pass 14.2 to 10 us); 1920 x 1152 under the pupil, N =
-// 52, c = 1/8: 442 to 251 us; N = 300, c = 1/16: 1250 to 863 us (no hand-off, no
-// update in the tail); mixed, N = 100: 502 to 362 us; 32 holograms of 1152^2 per
-// batch: 8.54 to 5.47 ms; 64 mixed ones 19.0 to 11.5 ms.  (The full-grid passes'
+// N = 100: 479 to 345 us (pass 14.2 to 10.1 us); 1920 x 1152 under the pupil, N =
+// 52, c = 1/8: 442 to 251 us; N = 300, c = 1/16: 1249 to 870 us (no hand-off, no
+// update in the tail); mixed, N = 100: 500 to 362 us; 32 holograms of 1152^2 per
+// batch: 8.62 to 5.66 ms; 64 mixed ones 19.0 to 11.7 ms.  (The full-grid passes'
 // own gains are in these.)
 #include <math.h>
 
@@ -146,7 +146,7 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   // sums of the units (64 lanes each), or of the chains (cl.stride spots each).
   // With two units per wave they take the wave's own pixel rows, which it has
   // read by then: 25.6 KB of LDS instead of 29.7, six blocks per compute unit
-  // instead of five (1920 x 1152, N = 300: 907 to 870 us per hologram).
+  // instead of five (1920 x 1152, N = 300: 903 to 874 us per hologram).
   __shared__ float2 red_own[MAXU > 1 ? 1 : kWaves * (CHAINS ? 2 : 1) * 64];
   float2* red = MAXU > 1 ? reinterpret_cast<float2*>(&px[0][0]) : red_own;
   static_assert(MAXU <= 2 && sizeof(px) == kWaves * 2 * 64 * sizeof(float2), "two units per row");
@@ -177,11 +177,11 @@ __device__ __forceinline__ void defer_tiles(const PassStart& h, const PassPlan& 
   // at half the rate.  Priorities that fall along the tile keep the blocks
   // level instead: all of them up to 256 spots, the last four of a compute
   // unit in mixed precision, the last six (as many as fit at once) beyond 256
-  // spots (N = 300 with four 870, with six 863 us per hologram).  1152^2, N =
-  // 100: 369 to 349 us (pass 10.75 to 10.05 us), mixed 372 to 362 us; N = 200,
-  // 2040 tiles 22.0 to 21.2 us; N = 512 50.5 to 48.8 us.
+  // spots (N = 300: without 920, with four 880, with six 874 us per hologram).
+  // 1152^2, N = 100: 365 to 346 us, mixed 371 to 362 us; N = 200, 2040 tiles 22.0 to
+  // 21.2 us; N = 512 50.5 to 48.8 us.
   // In launches of several tiles per block the blocks' phases interleave the
-  // better for it: 32 such holograms 5.65 to 5.48 ms, 64 mixed ones 12.1 to 11.5
+  // better for it: 32 such holograms 5.94 to 5.71 ms, 64 mixed ones 12.2 to 11.8
   // ms.  Up to 64 spots the additions at the blocks' ends bound the pass, and
   // even ends crowd them (N = 52, 2040 tiles: 9.0 to 10.7 us; ten holograms, two
   // tiles per block, N = 16: 31.4 to 32.2 us a round): there only launches of many

@@ -57,8 +57,8 @@ __global__ void k_metric_tables(SetupArgs a, SpotPtrs in, double2* __restrict__ 
 // v_mfma_f64_16x16x4_f64: A[l % 16][l / 16], B[l / 16][l % 16],
 // D[l / 16 + 4 r][l % 16] for lane l, r < 4.
 //
-// Bound: the FP64 matrix cores (8 W H Np operations, 15 us at 1152^2 and 112
-// spots and the 72 TFLOP/s that a large product reaches) and, beside them, a
+// Bound: the FP64 matrix cores (8 W H Np operations, 16.5 us at 1152^2 and 112
+// padded spots and the 72 TFLOP/s that a large product reaches) and, beside them, a
 // sine and cosine per pixel.  At 1152^2, N = 100: 33 us, and 5 us for the
 // reduction; one thread per spot over four rows, with every term's Ex from the
 // L2, took 671 us and its reduction (one thread per spot) 69 us.  The whole

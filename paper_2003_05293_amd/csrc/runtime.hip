@@ -1019,6 +1019,7 @@ void LaunchSet::launch(const JobDev* jobs, hipStream_t s, bool capture) const {
     else timed(s, name, f);
   };
   if (!sep.empty())
+    // (k_sep_pass: the tag that callers read for the iteration pass, k_sep_iter)
     run(sep_final ? "k_sep_final" : "k_sep_pass", [&] {
       launch_sep_pass(jobs, d_sep, (int)sep.size(), sep_blocks, sep_final, sep_steps, sep_start, s);
     });
